@@ -1125,7 +1125,11 @@ __device__ __forceinline__ void dw_reduce(const float* dwpart, const float* w_ne
 // Within the tile (causal, rows i >= j), with E_ij = phi_l(q_i) . phi_l(k_j) and
 // B_ij = g_i . v_j shared by the maps: dphi_l(k_j) += sum_i phi_l(q_i) (c B_ij /
 // den_i + dden_i), and dv_j += sum_i g_i sum_l c E_ij / den_i, one product for
-// all maps.
+// all maps.  The rows of the unit before the strip's are all earlier than its
+// keys and have weight zero, but a product with a zero still carries a NaN or
+// infinity: there both products read the strip's own unit instead (leaving
+// them out behind a branch spilled: whole forward and backward at 2^16 tokens
+// 551 us, 494 so).
 template <typename T, int D, bool CAUSAL, int R, bool TWO>
 __global__ __launch_bounds__(NT, TWO ? 2 : 1) void k_bwd_keys(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
@@ -1319,8 +1323,7 @@ __global__ __launch_bounds__(NT, TWO ? 2 : 1) void k_bwd_keys(
     }
     // ---- far field
     const T* gt = sg + tr * ST;  // the tile's dout rows
-    // g_i . v_j of the tile's rows (both units, masked where used: with a branch
-    // over the unit before the strip's the pass took 263 instead of 256 us)
+    // g_i . v_j of the tile's rows
     f32x4 B[2][2];
     if constexpr (CAUSAL) {
       if (!one_round) {
@@ -1416,10 +1419,11 @@ __global__ __launch_bounds__(NT, TWO ? 2 : 1) void k_bwd_keys(
               }
             }
             const Q c0q = f32_to_quad<T>(cc[0]), c1q = f32_to_quad<T>(cc[1]);
+            const T* pu = px + 32 * max(u, w >> 1) * ST;
 #pragma unroll
             for (int cb = 0; cb < NB; ++cb)
-              dph[cb] = mma_step2(ld_tquad(px, 32 * u, 16 * cb, ST),
-                                  ld_tquad(px, 32 * u + 16, 16 * cb, ST), c0q, c1q, dph[cb]);
+              dph[cb] = mma_step2(ld_tquad(pu, 0, 16 * cb, ST), ld_tquad(pu, 16, 16 * cb, ST),
+                                  c0q, c1q, dph[cb]);
           }
         }
         mfma_drain();
@@ -1436,10 +1440,11 @@ __global__ __launch_bounds__(NT, TWO ? 2 : 1) void k_bwd_keys(
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
           const Q e0 = f32_to_quad<T>(W[u][0]), e1 = f32_to_quad<T>(W[u][1]);
+          const T* gu = gt + 32 * max(u, w >> 1) * ST;
 #pragma unroll
           for (int eb = 0; eb < NB; ++eb)
-            dva[eb] = mma_step2(ld_tquad(gt, 32 * u, 16 * eb, ST),
-                                ld_tquad(gt, 32 * u + 16, 16 * eb, ST), e0, e1, dva[eb]);
+            dva[eb] = mma_step2(ld_tquad(gu, 0, 16 * eb, ST), ld_tquad(gu, 16, 16 * eb, ST), e0,
+                                e1, dva[eb]);
         }
         mfma_drain();
         // d = 128: the suffix record takes the tile's rows, unless this is the
