@@ -74,3 +74,54 @@ def test_state_carried_between_ranges():
     err = (out[rows].double() - want).norm(dim=-1) / want.norm(dim=-1)
     log(f"  worst row {err.max():.2e}")
     assert float(err.max()) < 1e-4
+
+
+def _dbeta_stepwise(q, k, v, beta, f, t):
+    """dbeta of sum(f * fw) by the recurrence, one step per position, in the
+    arithmetic of t; all slices [S, N, d] together."""
+    q, k, v, beta, f = (np.asarray(x).astype(t) for x in (q, k, v, beta, f))
+
+    def p(x):
+        phi = np.where(x > 0, x + t(1), np.exp(np.minimum(x, t(0))))
+        return phi / phi.sum(-1, keepdims=True)
+
+    def dot(x, y):  # [S, d, d] or [S, 1, d] times [S, d]
+        return np.matmul(x, y[..., None])[..., 0]
+
+    pq, pk = p(q), p(k)
+    s, n, d = q.shape
+    w, z = np.zeros((s, d, d), t), np.zeros((s, d), t)
+    e, den = [], []
+    for i in range(n):
+        e.append(v[:, i] - dot(w, pk[:, i]))
+        w = w + (beta[:, i, None] * e[-1])[..., None] * pk[:, i, None]
+        z = z + pk[:, i]
+        den.append((z * pq[:, i]).sum(-1, keepdims=True))
+    g, db = np.zeros((s, d, d), t), np.zeros((s, n), t)
+    for i in range(n - 1, -1, -1):
+        g = g + (f[:, i] / den[i])[..., None] * pq[:, i, None]
+        lam = dot(g, pk[:, i])
+        db[:, i] = (lam * e[i]).sum(-1)
+        g = g - (beta[:, i, None] * lam)[..., None] * pk[:, i, None]
+    return db
+
+
+@pytest.mark.parametrize("N,d", [(64, 16), (100, 32), (48, 64), (33, 128)])
+def test_dbeta_no_less_exact_than_single_steps(N, d):
+    # the yardstick is the recurrence itself in fp32: solving a chunk's
+    # triangular system must not lose what stepping through it keeps.  Errors
+    # are per slice (2-norm, relative), their geometric mean over 96 slices: it
+    # varies by about 0.5 / sqrt(96) = 5 % between inputs
+    S = 96
+    q, k, v, beta, _ = _inputs(S, 1, N, d, 900 + d)
+    dout = torch.randn(S, 1, N, d, device="cuda",
+                       generator=torch.Generator(device="cuda").manual_seed(d))
+    near, far = (torch.full((1,), x, device="cuda") for x in (-float("inf"), float("inf")))
+    got = binding.backward_fastweight(q, k, v, beta, dout, near, far, 0, 0)[3]
+    got = got[:, 0].double().cpu().numpy()
+    x = [y[:, 0].cpu().numpy() for y in (q, k, v, beta, dout)]
+    want, step = _dbeta_stepwise(*x, np.float64), _dbeta_stepwise(*x, np.float32)
+    err = [np.exp(np.log(np.linalg.norm(y - want, axis=1)
+                         / np.linalg.norm(want, axis=1)).mean()) for y in (got, step)]
+    log(f"dbeta N={N} d={d}: {err[0]:.3e}, in single steps {err[1]:.3e}")
+    assert err[0] <= err[1]
