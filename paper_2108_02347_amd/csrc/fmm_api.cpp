@@ -50,17 +50,62 @@ long long seg_rows(long long bh, int N, long long target_wg, int tm) {
   return L < tm ? tm : L;
 }
 
-// rec_share: a state record is at most 1 / rec_share of the K+V bytes it
-// summarises.
-Plan make_plan(int B, int H, int N, int d, int rank, int esize, int apply_tm,
-               int rec_share = 4) {
+// The smallest multiple of a tile's rows whose K + V bytes are `share` times
+// those of its state record.
+long long record_rows(int d, int rank, int esize, int share) {
   const int tm = fmm::tile_rows();
+  const long long l = 2LL * share * rank * (d + 1) / esize;
+  return std::max<long long>(tm, (l + tm - 1) / tm * tm);
+}
+
+// Rows of a state segment: ~512 workgroups, each segment's state record
+// (rank*d*(d+1) floats) at most a quarter of the K+V bytes it summarises.
+long long segment_rows(long long bh, int N, int d, int rank, int esize) {
+  return std::max(seg_rows(bh, N, 512, fmm::tile_rows()), record_rows(d, rank, esize, 4));
+}
+
+// Shorter ones, records of up to the K+V bytes themselves, where they leave at
+// most `wg` workgroups in all and `per_slice` in a slice (else segment_rows).
+// Up to one workgroup per CU a shorter walk is a shorter call; one more starts
+// a second round (fp32 causal, 8 slices of 9000 rows, d = 64, rank 2, whole
+// forward: 232 workgroups of 320 rows 106 us, 288 of 256 162, 376 of 192 126).
+long long fill_rows(long long bh, int N, int d, int rank, int esize, long long wg,
+                    long long per_slice) {
+  const long long base = segment_rows(bh, N, d, rank, esize);
+  const long long n = std::min(wg / bh, per_slice);
+  if (n < 1) return base;
+  const int tm = fmm::tile_rows();
+  const long long l = ((N + n - 1) / n + tm - 1) / tm * tm;
+  return std::min(base, std::max({l, seg_rows(bh, N, 512, tm), record_rows(d, rank, esize, 1)}));
+}
+
+constexpr long long kCUs = 256;
+// Segments of a slice beyond which the combine, which walks a slice's records
+// in four ranges and keeps the first 32 of each in registers, costs more than
+// the shorter walks save (one slice of 30000 rows, causal, us: bf16, d = 32,
+// rank 2, 118 segments 18.0, 157 19.2, 235 24.7, 469 44).  The fp32 walk, that
+// of rank 3 and the backward's cost more per row: up to 160 (10000 rows: fp32,
+// d = 32, rank 2, 79 segments 27.2, 157 22.7; bf16, d = 16, rank 3, 22.2, 19.2),
+// the causal fp32 one of wide heads up to one per CU (30000 rows, d = 64, rank
+// 2, 157 segments 69.2, 235 60.2).
+long long slice_segments(bool causal, int d, int rank, int esize, bool backward) {
+  if (esize == 2) return rank == 3 ? 192 : backward ? 160 : 128;
+  return causal && d >= 64 ? kCUs : 160;
+}
+
+// The rows of fill_rows for one workgroup per CU, or for two where that walk is
+// shorter by more than the second round costs: `round2` tenths of a first one.
+long long one_or_two_rows(long long bh, int N, int d, int rank, int esize, long long per_slice,
+                          int round2) {
+  const long long one = fill_rows(bh, N, d, rank, esize, kCUs, per_slice);
+  const long long two = fill_rows(bh, N, d, rank, esize, 2 * kCUs, per_slice);
+  auto cost = [&](long long L) { return L * (bh * ((N + L - 1) / L) <= kCUs ? 10 : round2); };
+  return cost(two) < cost(one) ? two : one;
+}
+
+// L: rows of a state segment.
+Plan make_plan(int B, int H, int N, int d, int rank, long long L, int apply_tm) {
   const long long bh = (long long)B * H;
-  // state segments: ~512 workgroups, but each segment's state record
-  // (rank*d*(d+1) floats) at most a quarter of the K+V bytes it summarises
-  long long L = seg_rows(bh, N, 512, tm);
-  const long long lmin = 2LL * rec_share * rank * (d + 1) / esize;
-  if (L < lmin) L = (lmin + tm - 1) / tm * tm;
   // non-causal apply walk: ~512 workgroups (two per CU), no state per segment
   const long long La = seg_rows(bh, N, 512, apply_tm);
   Plan p;
@@ -329,19 +374,23 @@ Plan plan_for(int B, int H, int N, int d, int band_k, int rank, int causal, int 
   const int apply_tm = fmm::band_pair_applies(dtype, d, kc, causal, N) ? fmm::pair_tile_rows()
                                                                     : fmm::tile_rows();
   const int es = dtype == FMM_DTYPE_BF16 ? 2 : 4;
-  Plan p = make_plan(B, H, N, d, rank, es, apply_tm);
   const long long bh = (long long)B * H;
-  // fewer state segments than CUs: records of up to half, then all, of the K+V
-  // bytes, where they fit the fixed array of the no-allocation call (so that
-  // it takes every shape that it took).  Whole calls: causal
-  // bf16, 2 slices of 3000 rows at d = 64 37.8 -> 20.6 us; 2 of 2521 rows at
-  // d = 128 454 -> 146 us; with CUs filled already, longer segments are as
-  // good and write less
-  for (int share = 2; share >= 1 && bh * p.nseg < 256; share /= 2) {
-    const Plan ps = make_plan(B, H, N, d, rank, es, apply_tm, share);
-    if (ps.ws_bytes == 0 || ps.ws_bytes > fmm_attn_noalloc_max_bytes()) break;
-    p = ps;
-  }
+  // one workgroup per CU where the records fit the fixed array of the
+  // no-allocation call (so that it takes every shape that it took).  Whole
+  // causal calls, us with quarter records -> so: bf16, 2 slices of 3000 rows at
+  // d = 64 36.9 -> 20.6; 2 of 16000 at d = 128 242 -> 88; fp32, 2 of 5000 at
+  // d = 32, rank 2 34.7 -> 19.5
+  const long long rec = (long long)rank * d * (d + 1) * (long long)sizeof(float);
+  const long long fit = (long long)fmm_attn_noalloc_max_bytes() / rec / bh - 1;
+  const long long most = std::min(slice_segments(causal, d, rank, es, false), fit);
+  // the causal walk of three maps fits twice on a CU (as in the backward; bf16,
+  // 32 slices of 4000 rows at d = 64: 256 workgroups 131 us, 512 100; 8 of 5000
+  // at d = 32: 216 35, 320 31); those of one or two gain nothing from a second
+  // round
+  const long long rows = causal && rank == 3
+                             ? one_or_two_rows(bh, N, d, rank, es, most, es == 2 ? 14 : 17)
+                             : fill_rows(bh, N, d, rank, es, kCUs, most);
+  Plan p = make_plan(B, H, N, d, rank, rows, apply_tm);
   add_fused(p, bh, fmm::fused_groups(dtype, d, kc, rank, causal, bh, N, kFusedPlanWorkgroups), d,
             rank);
   return p;
@@ -384,15 +433,21 @@ size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 // Workspace of the backward pass: the forward state records (as the forward
 // plan), the dS records of the same shape, per-row softmax statistics and far
 // quotients, and per-segment blend sums.  0 when it cannot exist.
-BwdPlan bwd_plan(int B, int H, int N, int d, int rank, int dtype) {
+BwdPlan bwd_plan(int B, int H, int N, int d, int rank, int causal, int dtype) {
   BwdPlan b;
-  // records of up to half the K+V bytes (the forward: a quarter): the backward
-  // reads K, V, q and dout twice beside them, and with longer segments its
-  // state kernels leave CUs idle (rank 3, d = 32, 16 slices of 4001 rows: 144
-  // workgroups; with 256, k_seg_grad 18.2 -> 12.4 us)
-  b.p = make_plan(B, H, N, d, rank, dtype == FMM_DTYPE_BF16 ? 2 : 4, fmm::tile_rows(), 2);
-  if ((long long)B * H * b.p.nseg < 256)  // (as plan_for)
-    b.p = make_plan(B, H, N, d, rank, dtype == FMM_DTYPE_BF16 ? 2 : 4, fmm::tile_rows(), 1);
+  // One workgroup per CU as in the forward, or two where the shorter walk makes
+  // up for it: two rounds cost 1.6 (causal bf16, two workgroups on a CU), 1.7
+  // (causal fp32) or 2.1 times one (non-causal: only the state kernels walk
+  // segments).  bf16 causal, d = 64, backward alone: 32 slices of 4000
+  // rows, rank 2, 224 workgroups of 576 rows 156 us, 256 of 512 144, 512 of 256
+  // 133; 8 of 9000, rank 1, 232 of 320 81, 376 of 192 75.  fp32, rank 2, 8 of
+  // 9000: 232 of 320 266 us, 376 of 192 319
+  const int es = dtype == FMM_DTYPE_BF16 ? 2 : 4;
+  const int round2 = !causal ? 21 : es == 2 ? 16 : 17;
+  b.p = make_plan(B, H, N, d, rank,
+                  one_or_two_rows((long long)B * H, N, d, rank, es,
+                                  slice_segments(causal, d, rank, es, true), round2),
+                  fmm::tile_rows());
   b.total = 0;
   if (b.p.ws_bytes == 0) return b;
   typedef unsigned __int128 u128;
@@ -454,7 +509,7 @@ int run_backward(const void* q, const void* k, const void* v, const void* dout, 
   if (overlaps(dq, dk, bytes) || overlaps(dq, dv, bytes) || overlaps(dk, dv, bytes))
     return FMM_ERR_INVALID_ARG;
   if (overlaps(dw_near, dw_far, (size_t)H * 4)) return FMM_ERR_INVALID_ARG;
-  const BwdPlan bp = bwd_plan(B, H, N, d, rank, dtype);
+  const BwdPlan bp = bwd_plan(B, H, N, d, rank, causal, dtype);
   if (bp.total == 0) return FMM_ERR_UNSUPPORTED;
   fmm::LaunchArgs fa = make_args(q, k, v, dq, B, H, N, d, band_k, rank, causal, w_near, w_far,
                                  dtype, FMM_FAR_NORM_PER_MAP, nullptr, bp.p, stream);
@@ -673,7 +728,7 @@ int run_layer_backward(const void* x, const void* w_qkv, const void* w_out, cons
   // workspace: qkv (later dqkv), q, k, v, o, m, dm, do, dq, dk, dv, then the
   // forward operator's and the backward's records
   const Plan p = plan_for(B, H, N, d, band_k, rank, causal, dtype);
-  const BwdPlan bp = bwd_plan(B, H, N, d, rank, dtype);
+  const BwdPlan bp = bwd_plan(B, H, N, d, rank, causal, dtype);
   if (p.ws_bytes == 0 || bp.total == 0) return FMM_ERR_UNSUPPORTED;
   const size_t seg = align256(xb);
   const size_t off_qkv = 0, off_q = 3 * seg, off_k = 4 * seg, off_v = 5 * seg, off_o = 6 * seg,
@@ -949,7 +1004,7 @@ int run_backward_fastweight(const void* q, const void* k, const void* v, const f
     if (overlaps2(dbeta, nb, o, bytes)) return FMM_ERR_INVALID_ARG;
   if (overlaps2(dbeta, nb, beta, nb) || overlaps(dw_near, dw_far, (size_t)H * 4))
     return FMM_ERR_INVALID_ARG;
-  const BwdPlan bp = bwd_plan(B, H, N, d, 1, dtype);
+  const BwdPlan bp = bwd_plan(B, H, N, d, 1, 1, dtype);
   if (bp.total == 0) return FMM_ERR_UNSUPPORTED;
   // after the backward's workspace: H floats of -inf, then the fast-weight
   // kernels' chunks

@@ -322,8 +322,20 @@ hipError_t launch_wide_k(const LaunchArgs& a, Launcher& L, float* recs) {
   // the causal walk starts from its state segment's prefix; the non-causal
   // one needs only the slice's totals and takes the apply split of about two
   // workgroups per CU (rank 3, d = 32, 16 slices of 4001 rows: 144 -> 512
-  // workgroups, 23.3 -> 9.6 us)
-  const int nseg = CAUSAL ? a.nseg : a.nseg_apply, Lw = CAUSAL ? a.L : a.L_apply;
+  // workgroups, 23.3 -> 9.6 us); where only one fits on a CU, about one, if the
+  // second round costs more than the longer walk (fp32, d = 128, 8 slices of
+  // 9000 rows: 232 workgroups of five tiles 152 us per call, 376 of three 182)
+  int nseg = CAUSAL ? a.nseg : a.nseg_apply, Lw = CAUSAL ? a.L : a.L_apply;
+  if constexpr (!CAUSAL && !TWO) {
+    const long long cus = 256, bh = (long long)a.B * a.H;
+    const long long per = std::max<long long>(1, cus / bh);
+    const long long l = (a.N + per * TM - 1) / (per * TM) * TM;
+    auto cost = [&](long long x) { return (bh * ((a.N + x - 1) / x) + cus - 1) / cus * (x / TM); };
+    if (cost(l) < cost(Lw)) {
+      Lw = (int)l;
+      nseg = (int)((a.N + l - 1) / l);
+    }
+  }
   L(a.causal ? FMM_KERNEL_CAUSAL_APPLY : FMM_KERNEL_BAND_APPLY, k_wide<T, D, CAUSAL, JOINT, TWO>,
     dim3(a.B * a.H * nseg), dim3(NT), (size_t)C::LDS, (hipStream_t)a.stream, (const T*)a.q,
     (const T*)a.k, (const T*)a.v, (T*)a.out, recs, a.w_near, a.w_far, a.H, a.N, a.band_k, Lw,
