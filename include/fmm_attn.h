@@ -285,8 +285,9 @@ int fmm_attn_layer_forward(const void* x, const void* w_qkv, const void* w_out, 
  *             dw_near, dw_far: device float[H].  No output may overlap an
  *             input or another output.
  * The forward is recomputed (the projections, the operator); the
- * intermediates live in the library-owned workspace (13 token-by-E arrays
- * beside the operator's records).  Errors as fmm_attn_layer_forward.
+ * intermediates live in the library-owned workspace (8 token-by-E arrays, 13
+ * around rocBLAS products, beside the operator's records).  Errors as
+ * fmm_attn_layer_forward.
  */
 int fmm_attn_layer_backward(const void* x, const void* w_qkv, const void* w_out, const void* dy,
                             void* dx, void* dw_qkv, void* dw_out, float* dw_near, float* dw_far,

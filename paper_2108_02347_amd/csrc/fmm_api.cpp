@@ -598,14 +598,14 @@ int run_layer(const void* x, const void* w_qkv, const void* w_out, void* y, int 
   const size_t xb = (size_t)xbytes, wq = (size_t)E * 3 * E * es, wo = (size_t)E * E * es;
   if (overlaps2(y, xb, x, xb) || overlaps2(y, xb, w_qkv, wq) || overlaps2(y, xb, w_out, wo))
     return FMM_ERR_INVALID_ARG;
-  // workspace: qkv, q, k, v, o, merged heads, then the operator's records
-  // (with the library's own projection kernels only q, k, v and o are used)
+  // workspace: the heads q, k, v and their outputs o, around rocBLAS products
+  // also qkv and the merged heads m, then the operator's records
   const Plan p = plan_for(B, H, N, d, band_k, rank, causal, dtype);
   if (p.ws_bytes == 0) return FMM_ERR_UNSUPPORTED;
   const bool own_proj = fmm::layer_proj_applies(E);
   const size_t seg = align256(xb);
-  const size_t off_qkv = 0, off_q = 3 * seg, off_k = 4 * seg, off_v = 5 * seg, off_o = 6 * seg,
-               off_m = 7 * seg, off_ws = 8 * seg;
+  const size_t off_q = 0, off_k = seg, off_v = 2 * seg, off_o = 3 * seg, off_qkv = 4 * seg,
+               off_m = 7 * seg, off_ws = own_proj ? 4 * seg : 8 * seg;
   const size_t total = off_ws + p.ws_bytes;
   auto at = [](void* base, size_t off) {
     return reinterpret_cast<void*>(reinterpret_cast<uintptr_t>(base) + off);
@@ -635,9 +635,13 @@ int run_layer(const void* x, const void* w_qkv, const void* w_out, void* y, int 
     if (dry.err != hipSuccess)
       return dry.err == hipErrorInvalidConfiguration ? FMM_ERR_UNSUPPORTED : FMM_ERR_HIP;
   }
-  std::lock_guard<std::mutex> bl(blas_mutex());
-  void* hdl = blas_handle();
-  if (!hdl) return FMM_ERR_HIP;
+  std::unique_lock<std::mutex> bl(blas_mutex(), std::defer_lock);
+  void* hdl = nullptr;  // (the library's own products need none)
+  if (!own_proj) {
+    bl.lock();
+    hdl = blas_handle();
+    if (!hdl) return FMM_ERR_HIP;
+  }
   std::lock_guard<std::mutex> wl(ws_mutex());
   void* ws = nullptr;
   st = acquire_ws_locked(stream, total, &ws);
@@ -723,17 +727,17 @@ int run_layer_backward(const void* x, const void* w_qkv, const void* w_out, cons
   }
   if (overlaps(dw_near, dw_far, (size_t)H * 4)) return FMM_ERR_INVALID_ARG;
   const bool own_proj = fmm::layer_proj_applies(E);
-  // (with the library's own projection kernels only q, k, v, o, do, dq, dk and
-  // dv are used)
-  // workspace: qkv (later dqkv), q, k, v, o, m, dm, do, dq, dk, dv, then the
-  // forward operator's and the backward's records
+  // workspace: the heads q, k, v, their outputs o and the gradients do, dq, dk,
+  // dv, around rocBLAS products also qkv (later dqkv), m and dm, then the
+  // forward operator's and the backward's records and the weight gradients'
+  // chunks
   const Plan p = plan_for(B, H, N, d, band_k, rank, causal, dtype);
   const BwdPlan bp = bwd_plan(B, H, N, d, rank, causal, dtype);
   if (p.ws_bytes == 0 || bp.total == 0) return FMM_ERR_UNSUPPORTED;
   const size_t seg = align256(xb);
-  const size_t off_qkv = 0, off_q = 3 * seg, off_k = 4 * seg, off_v = 5 * seg, off_o = 6 * seg,
-               off_m = 7 * seg, off_dm = 8 * seg, off_do = 9 * seg, off_dq = 10 * seg,
-               off_dk = 11 * seg, off_dv = 12 * seg, off_fws = 13 * seg,
+  const size_t off_q = 0, off_k = seg, off_v = 2 * seg, off_o = 3 * seg, off_do = 4 * seg,
+               off_dq = 5 * seg, off_dk = 6 * seg, off_dv = 7 * seg, off_qkv = 8 * seg,
+               off_m = 11 * seg, off_dm = 12 * seg, off_fws = own_proj ? 8 * seg : 13 * seg,
                off_bws = off_fws + align256(p.ws_bytes),
                off_wg = off_bws + align256(bp.total);
   const int Mtok = B * N;  // fits: checked above
@@ -803,9 +807,13 @@ int run_layer_backward(const void* x, const void* w_qkv, const void* w_out, cons
     if (dry.err != hipSuccess)
       return dry.err == hipErrorInvalidConfiguration ? FMM_ERR_UNSUPPORTED : FMM_ERR_HIP;
   }
-  std::lock_guard<std::mutex> bl(blas_mutex());
-  void* hdl = blas_handle();
-  if (!hdl) return FMM_ERR_HIP;
+  std::unique_lock<std::mutex> bl(blas_mutex(), std::defer_lock);
+  void* hdl = nullptr;  // (the library's own products need none)
+  if (!own_proj) {
+    bl.lock();
+    hdl = blas_handle();
+    if (!hdl) return FMM_ERR_HIP;
+  }
   std::lock_guard<std::mutex> wl(ws_mutex());
   void* ws = nullptr;
   st = acquire_ws_locked(stream, total, &ws);
