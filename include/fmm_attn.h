@@ -179,7 +179,10 @@ size_t fmm_attn_workspace_bytes(int B, int H, int N, int d, int rank, int causal
  * fmm_attn_forward_ws - the operator with a caller-owned device workspace of
  * at least fmm_attn_workspace_bytes(...) bytes, 256-byte aligned.  dtype is
  * FMM_DTYPE_F32 or FMM_DTYPE_BF16.  Allocates nothing.  Calls that overlap in
- * time must not share a workspace.  FMM_ERR_OOM if ws_bytes is too small.
+ * time must not share a workspace.  FMM_ERR_OOM if ws_bytes is too small; this
+ * call and those with the library-owned workspace do with less than that where
+ * longer segments need less (down to one state record per quarter of its size
+ * in k and v).
  */
 int fmm_attn_forward_ws(const void* q, const void* k, const void* v, void* out,
                         int B, int H, int N, int d, int band_k, int rank,
@@ -310,9 +313,10 @@ int fmm_attn_layer_backward(const void* x, const void* w_qkv, const void* w_out,
  *   n_linear: 0 or 1.
  * Other arguments as fmm_attn_forward_ex (dtype FMM_DTYPE_F32 or _BF16).  The
  * recurrence runs in chunks of 16 positions, in fp32, one chunk after the
- * other.  Uses the library-owned workspace (beside the operator's records at
- * most 1 GiB: 5 d + d (d + 1) / 16 + 2 floats per position, longer or larger
- * calls in several passes over it).
+ * other.  Uses the library-owned workspace (in the place of the operator's
+ * records, once those are done with: 5 d + d (d + 1) / 16 + 2 floats per
+ * position, but at most 1 GiB or what can be had, longer or larger calls in
+ * several passes over it).
  */
 int fmm_attn_forward_fastweight(const void* q, const void* k, const void* v,
                                 const float* beta, void* out, int B, int H, int N, int d,
@@ -330,8 +334,8 @@ int fmm_attn_forward_fastweight(const void* q, const void* k, const void* v,
  * beta_{i+1} p(k_{i+1}) p(k_{i+1})^T), from which dv_i = beta_i G_i p(k_i),
  * dbeta_i = (v_i - u_i) . G_i p(k_i) and the key and query gradients follow;
  * the near field and the linear part are those of fmm_attn_backward (rank 1,
- * causal).  The library-owned workspace holds, beside the backward's own,
- * 6 d + d (d + 1) / 8 + 4 floats per position.  No output may overlap an input
+ * causal).  The library-owned workspace holds, in the place of the backward's
+ * own, 6 d + d (d + 1) / 8 + 4 floats per position.  No output may overlap an input
  * or another output.  Errors as fmm_attn_backward.
  */
 int fmm_attn_backward_fastweight(const void* q, const void* k, const void* v,

@@ -221,7 +221,8 @@ size_t ws_limit() {
 // Returns a workspace of at least `bytes` for (current device, stream).  The
 // caller holds ws_mutex() until its kernels are enqueued, so no other thread
 // can free the buffer between this lookup and the launches that use it.
-int acquire_ws_locked(void* stream, size_t bytes, void** out) {
+// keep: the caller can do with less, so a failure leaves the present buffer.
+int acquire_ws_locked(void* stream, size_t bytes, void** out, bool keep = false) {
   if (bytes > ws_limit()) return FMM_ERR_OOM;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return FMM_ERR_HIP;
@@ -235,15 +236,22 @@ int acquire_ws_locked(void* stream, size_t bytes, void** out) {
       return FMM_ERR_HIP;
     }
     if (cs != hipStreamCaptureStatusNone) return FMM_ERR_UNSUPPORTED;
+    void* p = nullptr;
+    if (keep && hipMalloc(&p, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return FMM_ERR_OOM;
+    }
     if (e.ptr) {
       // kernels enqueued earlier on this stream may still read the old buffer
-      if (hipStreamSynchronize((hipStream_t)stream) != hipSuccess) return FMM_ERR_HIP;
+      if (hipStreamSynchronize((hipStream_t)stream) != hipSuccess) {
+        if (p) (void)hipFree(p);
+        return FMM_ERR_HIP;
+      }
       (void)hipFree(e.ptr);
       e.ptr = nullptr;
       e.bytes = 0;
     }
-    void* p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) {
+    if (!p && hipMalloc(&p, bytes) != hipSuccess) {
       (void)hipGetLastError();
       return FMM_ERR_OOM;
     }
@@ -252,6 +260,16 @@ int acquire_ws_locked(void* stream, size_t bytes, void** out) {
   }
   *out = e.ptr;
   return FMM_OK;
+}
+
+// Runs f(lean) with the preferred plan, then, where its workspace was not to be
+// had (the limit, the device's memory, the caller's buffer, or a capture that
+// finds a smaller one), with the leanest: what the shorter segments took is no
+// reason to refuse a call.  f returns FMM_ERR_OOM, or FMM_ERR_UNSUPPORTED, only
+// before it has enqueued anything.
+template <typename F> int preferred_or_lean(F f) {
+  const int st = f(false);
+  return st == FMM_ERR_OOM || st == FMM_ERR_UNSUPPORTED ? f(true) : st;
 }
 
 // The dry pass over the launch sequence: grid limits and LDS limits, nothing
@@ -369,7 +387,10 @@ void add_fused(Plan& p, long long bh, int G, int d, int rank) {
   if (f > p.ws_bytes) p.ws_bytes = f;
 }
 
-Plan plan_for(int B, int H, int N, int d, int band_k, int rank, int causal, int dtype) {
+// lean: the plan of the smallest workspace (segment_rows), for where the
+// preferred one's is not to be had.
+Plan plan_for(int B, int H, int N, int d, int band_k, int rank, int causal, int dtype,
+              bool lean = false) {
   const int kc = band_k < N ? band_k : N;
   const int apply_tm = fmm::band_pair_applies(dtype, d, kc, causal, N) ? fmm::pair_tile_rows()
                                                                     : fmm::tile_rows();
@@ -379,15 +400,25 @@ Plan plan_for(int B, int H, int N, int d, int band_k, int rank, int causal, int 
   // no-allocation call (so that it takes every shape that it took).  Whole
   // causal calls, us with quarter records -> so: bf16, 2 slices of 3000 rows at
   // d = 64 36.9 -> 20.6; 2 of 16000 at d = 128 242 -> 88; fp32, 2 of 5000 at
-  // d = 32, rank 2 34.7 -> 19.5
+  // d = 64, rank 2 97.8 -> 45.6
   const long long rec = (long long)rank * d * (d + 1) * (long long)sizeof(float);
   const long long fit = (long long)fmm_attn_noalloc_max_bytes() / rec / bh - 1;
-  const long long most = std::min(slice_segments(causal, d, rank, es, false), fit);
+  const long long base = segment_rows(bh, N, d, rank, es);
+  long long most = std::min(slice_segments(causal, d, rank, es, false), fit);
+  // narrow heads, one or two maps: less than twice the workspace (so that half
+  // of what fmm_attn_workspace_bytes states is never enough); it holds back
+  // fp32, d = 32, rank 2 on a few slices only (2 of 5000 27 us, 19.5 with four
+  // times the records, 35 with the longest segments)
+  if (d <= 32 && rank <= 2) most = std::min(most, 2 * ((N + base - 1) / base));
   // the causal walk of three maps fits twice on a CU (as in the backward; bf16,
   // 32 slices of 4000 rows at d = 64: 256 workgroups 131 us, 512 100; 8 of 5000
   // at d = 32: 216 35, 320 31); those of one or two gain nothing from a second
   // round
-  const long long rows = causal && rank == 3
+  // (non-causal only the state kernel walks segments: with narrow heads and one
+  // or two maps most calls take as long either way, the best gain 5 %)
+  const bool same = !causal && d <= 32 && rank <= 2;
+  const long long rows = lean || same ? base
+                         : causal && rank == 3
                              ? one_or_two_rows(bh, N, d, rank, es, most, es == 2 ? 14 : 17)
                              : fill_rows(bh, N, d, rank, es, kCUs, most);
   Plan p = make_plan(B, H, N, d, rank, rows, apply_tm);
@@ -397,13 +428,14 @@ Plan plan_for(int B, int H, int N, int d, int band_k, int rank, int causal, int 
 }
 
 
-int run(const void* q, const void* k, const void* v, void* out, int B, int H, int N, int d,
-        int band_k, int rank, int causal, const float* w_near, const float* w_far, int dtype,
-        int far_norm, void* ws, size_t ws_bytes, bool own_ws, void* stream) {
+int run_plan(const void* q, const void* k, const void* v, void* out, int B, int H, int N, int d,
+             int band_k, int rank, int causal, const float* w_near, const float* w_far,
+             int dtype, int far_norm, void* ws, size_t ws_bytes, bool own_ws, void* stream,
+             bool lean) {
   int st = validate(q, k, v, out, B, H, N, d, band_k, rank, causal, w_near, w_far, dtype,
                     far_norm);
   if (st != FMM_OK) return st;
-  const Plan p = plan_for(B, H, N, d, band_k, rank, causal, dtype);
+  const Plan p = plan_for(B, H, N, d, band_k, rank, causal, dtype, lean);
   if (p.ws_bytes == 0) return FMM_ERR_UNSUPPORTED;
   fmm::LaunchArgs a = make_args(q, k, v, out, B, H, N, d, band_k, rank, causal, w_near, w_far,
                                 dtype, far_norm, nullptr, p, stream);
@@ -412,7 +444,7 @@ int run(const void* q, const void* k, const void* v, void* out, int B, int H, in
   std::unique_lock<std::mutex> ws_lock(ws_mutex(), std::defer_lock);
   if (own_ws) {
     ws_lock.lock();
-    st = acquire_ws_locked(stream, p.ws_bytes, &ws);
+    st = acquire_ws_locked(stream, p.ws_bytes, &ws, !lean);
     if (st != FMM_OK) return st;
   } else {
     if (!ws || (uintptr_t)ws % 256) return FMM_ERR_INVALID_ARG;
@@ -422,9 +454,19 @@ int run(const void* q, const void* k, const void* v, void* out, int B, int H, in
   return launch_now(a);
 }
 
+int run(const void* q, const void* k, const void* v, void* out, int B, int H, int N, int d,
+        int band_k, int rank, int causal, const float* w_near, const float* w_far, int dtype,
+        int far_norm, void* ws, size_t ws_bytes, bool own_ws, void* stream) {
+  return preferred_or_lean([&](bool lean) {
+    return run_plan(q, k, v, out, B, H, N, d, band_k, rank, causal, w_near, w_far, dtype,
+                    far_norm, ws, ws_bytes, own_ws, stream, lean);
+  });
+}
+
 // ------------------------------------------------------------------ backward
 struct BwdPlan {
   Plan p;
+  int nwalk, Lwalk;  // row segments of the row and key passes
   size_t off_dpart, off_rowstat, off_rowfar, off_dwpart, total;
 };
 
@@ -432,8 +474,10 @@ size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
 // Workspace of the backward pass: the forward state records (as the forward
 // plan), the dS records of the same shape, per-row softmax statistics and far
-// quotients, and per-segment blend sums.  0 when it cannot exist.
-BwdPlan bwd_plan(int B, int H, int N, int d, int rank, int causal, int dtype) {
+// quotients, and per-segment blend sums.  0 when it cannot exist.  lean: as
+// plan_for.
+BwdPlan bwd_plan(int B, int H, int N, int d, int rank, int causal, int dtype,
+                 bool lean = false) {
   BwdPlan b;
   // One workgroup per CU as in the forward, or two where the shorter walk makes
   // up for it: two rounds cost 1.6 (causal bf16, two workgroups on a CU), 1.7
@@ -444,17 +488,27 @@ BwdPlan bwd_plan(int B, int H, int N, int d, int rank, int causal, int dtype) {
   // 9000: 232 of 320 266 us, 376 of 192 319
   const int es = dtype == FMM_DTYPE_BF16 ? 2 : 4;
   const int round2 = !causal ? 21 : es == 2 ? 16 : 17;
+  const long long bh = (long long)B * H;
   b.p = make_plan(B, H, N, d, rank,
-                  one_or_two_rows((long long)B * H, N, d, rank, es,
-                                  slice_segments(causal, d, rank, es, true), round2),
+                  lean ? segment_rows(bh, N, d, rank, es)
+                       : one_or_two_rows(bh, N, d, rank, es,
+                                         slice_segments(causal, d, rank, es, true), round2),
                   fmm::tile_rows());
+  // the causal walks start from their segment's prefix (suffix) record; the
+  // non-causal ones need only the slice's totals and take the apply split of
+  // about two workgroups per CU (row / key pass, us: rank 3, 16 slices of 4001
+  // rows, 144 -> 512 workgroups and two per CU 41.7 / 28.6 -> 20.0 / 14.4;
+  // fp32, 64 slices of 1024 rows, 384 -> 512 workgroups 54.9 / 40.1 ->
+  // 41.4 / 32.5)
+  b.nwalk = causal || lean ? b.p.nseg : b.p.nseg_apply;
+  b.Lwalk = causal || lean ? b.p.L : b.p.L_apply;
   b.total = 0;
   if (b.p.ws_bytes == 0) return b;
   typedef unsigned __int128 u128;
   const u128 bhn = (u128)B * H * N;
   const u128 rowstat = (u128)align256((size_t)std::min<u128>(bhn * 12, SIZE_MAX / 8));
   const u128 rowfar = (u128)align256((size_t)std::min<u128>(bhn * rank * 8, SIZE_MAX / 8));
-  const u128 dwp = align256((size_t)B * H * std::max(b.p.nseg, b.p.nseg_apply) * 8);
+  const u128 dwp = align256((size_t)bh * b.nwalk * 8);
   const u128 tot = 2 * (u128)b.p.ws_bytes + rowstat + rowfar + dwp;
   if (tot > (u128)(SIZE_MAX / 4)) return b;
   b.off_dpart = b.p.ws_bytes;
@@ -476,20 +530,14 @@ void fill_bwd_args(fmm::BwdArgs& a, const BwdPlan& bp, void* ws, int B, int H) {
   a.rowstat = reinterpret_cast<float*>(w + bp.off_rowstat);
   a.rowfar = reinterpret_cast<float*>(w + bp.off_rowfar);
   a.dwpart = reinterpret_cast<float*>(w + bp.off_dwpart);
-  // the causal walks start from their segment's prefix (suffix) record; the
-  // non-causal ones need only the slice's totals and take the apply split of
-  // about two workgroups per CU (row / key pass, us: rank 3, 16 slices of 4001
-  // rows, 144 -> 512 workgroups and two per CU 41.7 / 28.6 -> 20.0 / 14.4;
-  // fp32, 64 slices of 1024 rows, 384 -> 512 workgroups 54.9 / 40.1 ->
-  // 41.4 / 32.5)
-  a.nwalk = a.causal ? bp.p.nseg : bp.p.nseg_apply;
-  a.Lwalk = a.causal ? bp.p.L : bp.p.L_apply;
+  a.nwalk = bp.nwalk;
+  a.Lwalk = bp.Lwalk;
 }
 
 int run_backward(const void* q, const void* k, const void* v, const void* dout, void* dq,
                  void* dk, void* dv, float* dw_near, float* dw_far, int B, int H, int N, int d,
                  int band_k, int rank, int causal, const float* w_near, const float* w_far,
-                 int dtype, int far_norm, void* stream) {
+                 int dtype, int far_norm, void* stream, bool lean) {
   // the inputs as in the forward (dout takes the place of out for the checks)
   int st = validate(q, k, v, dq, B, H, N, d, band_k, rank, causal, w_near, w_far, dtype,
                     far_norm);
@@ -509,7 +557,7 @@ int run_backward(const void* q, const void* k, const void* v, const void* dout, 
   if (overlaps(dq, dk, bytes) || overlaps(dq, dv, bytes) || overlaps(dk, dv, bytes))
     return FMM_ERR_INVALID_ARG;
   if (overlaps(dw_near, dw_far, (size_t)H * 4)) return FMM_ERR_INVALID_ARG;
-  const BwdPlan bp = bwd_plan(B, H, N, d, rank, causal, dtype);
+  const BwdPlan bp = bwd_plan(B, H, N, d, rank, causal, dtype, lean);
   if (bp.total == 0) return FMM_ERR_UNSUPPORTED;
   fmm::LaunchArgs fa = make_args(q, k, v, dq, B, H, N, d, band_k, rank, causal, w_near, w_far,
                                  dtype, FMM_FAR_NORM_PER_MAP, nullptr, bp.p, stream);
@@ -550,7 +598,7 @@ int run_backward(const void* q, const void* k, const void* v, const void* dout, 
   }
   std::lock_guard<std::mutex> wl(ws_mutex());
   void* ws = nullptr;
-  st = acquire_ws_locked(stream, bp.total, &ws);
+  st = acquire_ws_locked(stream, bp.total, &ws, !lean);
   if (st != FMM_OK) return st;
   fa.ws = (float*)ws;
   fill_bwd_args(ba, bp, ws, B, H);
@@ -579,7 +627,7 @@ void* blas_handle() {
 
 int run_layer(const void* x, const void* w_qkv, const void* w_out, void* y, int B, int N, int E,
               int H, int band_k, int rank, int causal, const float* w_near, const float* w_far,
-              int dtype, void* stream) {
+              int dtype, void* stream, bool lean) {
   if (!x || !w_qkv || !w_out || !y || !w_near || !w_far) return FMM_ERR_INVALID_ARG;
   if (B < 1 || N < 1 || E < 1 || H < 1 || band_k < 0 || E % H) return FMM_ERR_INVALID_ARG;
   if (causal != 0 && causal != 1) return FMM_ERR_INVALID_ARG;
@@ -600,7 +648,7 @@ int run_layer(const void* x, const void* w_qkv, const void* w_out, void* y, int 
     return FMM_ERR_INVALID_ARG;
   // workspace: the heads q, k, v and their outputs o, around rocBLAS products
   // also qkv and the merged heads m, then the operator's records
-  const Plan p = plan_for(B, H, N, d, band_k, rank, causal, dtype);
+  const Plan p = plan_for(B, H, N, d, band_k, rank, causal, dtype, lean);
   if (p.ws_bytes == 0) return FMM_ERR_UNSUPPORTED;
   const bool own_proj = fmm::layer_proj_applies(E);
   const size_t seg = align256(xb);
@@ -644,7 +692,7 @@ int run_layer(const void* x, const void* w_qkv, const void* w_out, void* y, int 
   }
   std::lock_guard<std::mutex> wl(ws_mutex());
   void* ws = nullptr;
-  st = acquire_ws_locked(stream, total, &ws);
+  st = acquire_ws_locked(stream, total, &ws, !lean);
   if (st != FMM_OK) return st;
   a.q = at(ws, off_q);
   a.k = at(ws, off_k);
@@ -692,7 +740,7 @@ int run_layer(const void* x, const void* w_qkv, const void* w_out, void* y, int 
 int run_layer_backward(const void* x, const void* w_qkv, const void* w_out, const void* dy,
                        void* dx, void* dw_qkv, void* dw_out, float* dw_near, float* dw_far,
                        int B, int N, int E, int H, int band_k, int rank, int causal,
-                       const float* w_near, const float* w_far, int dtype, void* stream) {
+                       const float* w_near, const float* w_far, int dtype, void* stream, bool lean) {
   if (!x || !w_qkv || !w_out || !dy || !dx || !dw_qkv || !dw_out || !dw_near || !dw_far ||
       !w_near || !w_far)
     return FMM_ERR_INVALID_ARG;
@@ -731,8 +779,8 @@ int run_layer_backward(const void* x, const void* w_qkv, const void* w_out, cons
   // dv, around rocBLAS products also qkv (later dqkv), m and dm, then the
   // forward operator's and the backward's records and the weight gradients'
   // chunks
-  const Plan p = plan_for(B, H, N, d, band_k, rank, causal, dtype);
-  const BwdPlan bp = bwd_plan(B, H, N, d, rank, causal, dtype);
+  const Plan p = plan_for(B, H, N, d, band_k, rank, causal, dtype, lean);
+  const BwdPlan bp = bwd_plan(B, H, N, d, rank, causal, dtype, lean);
   if (p.ws_bytes == 0 || bp.total == 0) return FMM_ERR_UNSUPPORTED;
   const size_t seg = align256(xb);
   const size_t off_q = 0, off_k = seg, off_v = 2 * seg, off_o = 3 * seg, off_do = 4 * seg,
@@ -741,7 +789,8 @@ int run_layer_backward(const void* x, const void* w_qkv, const void* w_out, cons
                off_bws = off_fws + align256(p.ws_bytes),
                off_wg = off_bws + align256(bp.total);
   const int Mtok = B * N;  // fits: checked above
-  const size_t total = off_wg + align256(fmm::layer_wgrad_scratch_bytes(Mtok, E, 3 * E));
+  const size_t total =
+      off_wg + align256(fmm::layer_wgrad_scratch_bytes(Mtok, E, 3 * E, lean));
   auto at = [](void* base, size_t off) {
     return reinterpret_cast<void*>(reinterpret_cast<uintptr_t>(base) + off);
   };
@@ -790,7 +839,7 @@ int run_layer_backward(const void* x, const void* w_qkv, const void* w_out, cons
                                      nullptr, nullptr, B, N, H, d, s);
       for (bool qkv : {false, true})
         (void)fmm::launch_layer_wgrad(dry, dtype, qkv, nullptr, nullptr, nullptr, nullptr,
-                                      nullptr, nullptr, B, N, H, d, s);
+                                      nullptr, nullptr, B, N, H, d, s, lean);
     } else {
       (void)fmm::launch_layer_copy(dry, true, dtype, nullptr, nullptr, nullptr, nullptr, B, N, H,
                                    d, s);
@@ -816,7 +865,7 @@ int run_layer_backward(const void* x, const void* w_qkv, const void* w_out, cons
   }
   std::lock_guard<std::mutex> wl(ws_mutex());
   void* ws = nullptr;
-  st = acquire_ws_locked(stream, total, &ws);
+  st = acquire_ws_locked(stream, total, &ws, !lean);
   if (st != FMM_OK) return st;
   a.q = ba.q = at(ws, off_q);
   a.k = ba.k = at(ws, off_k);
@@ -848,14 +897,14 @@ int run_layer_backward(const void* x, const void* w_qkv, const void* w_out, cons
         fmm::launch_layer_proj(L, fmm::LayerProj::kDm, dtype, dy, nullptr, nullptr, w_out,
                                at(ws, off_do), nullptr, nullptr, B, N, H, d, s) != hipSuccess ||
         fmm::launch_layer_wgrad(L, dtype, false, a.out, dy, nullptr, nullptr, dw_out, wgs, B, N,
-                                H, d, s) != hipSuccess ||
+                                H, d, s, lean) != hipSuccess ||
         fmm::launch_state_only(fa, L) != hipSuccess ||
         fmm::launch_backward_tail(ba, L) != hipSuccess ||
         fmm::launch_layer_proj(L, fmm::LayerProj::kDx, dtype, ba.dq, ba.dk, ba.dv, w_qkv, dx,
                                nullptr, nullptr, B, N, H, d, s) != hipSuccess)
       return FMM_ERR_HIP;
     return fmm::launch_layer_wgrad(L, dtype, true, x, ba.dq, ba.dk, ba.dv, dw_qkv, wgs, B, N, H,
-                                   d, s) == hipSuccess
+                                   d, s, lean) == hipSuccess
                ? FMM_OK
                : FMM_ERR_HIP;
   }
@@ -918,20 +967,30 @@ int run_layer_backward(const void* x, const void* w_qkv, const void* w_out, cons
 }
 
 // ------------------------------------------------------------------ fast weight
+// level: 0 the preferred plan, 1 the leanest of the operator, then passes of
+// half the chunks each time.  *last: a further level would take no less.
 int run_fastweight(const void* q, const void* k, const void* v, const float* beta, void* out,
                    int B, int H, int N, int d, int band_k, int n_linear, const float* w_near,
-                   const float* w_far, int dtype, void* stream) {
+                   const float* w_far, int dtype, void* stream, int level, bool* last) {
+  *last = true;
   int st = validate(q, k, v, out, B, H, N, d, band_k, 1, 1, w_near, w_far, dtype,
                     FMM_FAR_NORM_PER_MAP);
   if (st != FMM_OK) return st;
   if (!beta || (uintptr_t)beta % 4 || (n_linear != 0 && n_linear != 1))
     return FMM_ERR_INVALID_ARG;
-  const Plan p = plan_for(B, H, N, d, band_k, 1, 1, dtype);
+  const Plan p = plan_for(B, H, N, d, band_k, 1, 1, dtype, level > 0);
   if (p.ws_bytes == 0) return FMM_ERR_UNSUPPORTED;
-  // the operator's records, then H floats of -inf that remove its linear
-  // far part when n_linear = 0, then the fast-weight kernels' chunks
-  const size_t total = p.ws_bytes + align256((size_t)H * 4) +
-                       align256(fmm::fw_forward_bytes((long long)B * H, N, d));
+  // the operator's records, then H floats of -inf that remove its linear far
+  // part when n_linear = 0; once its kernels have run, the fast-weight kernels'
+  // chunks in the same place
+  const long long bh = (long long)B * H;
+  const size_t pass = level < 2 ? fmm::kFwPassBytes
+                                : fmm::fw_forward_bytes(bh, N, d, fmm::kFwPassBytes) >>
+                                      std::min(level - 1, 60);
+  const fmm::FwPlan fp = fmm::fw_plan(bh, N, d, pass);
+  *last = level > 0 && fp.slices == 1 && fp.chunks == 1;
+  const size_t total = std::max(p.ws_bytes + align256((size_t)H * 4),
+                                align256(fmm::fw_forward_bytes(bh, N, d, pass)));
   fmm::LaunchArgs a = make_args(q, k, v, out, B, H, N, d, band_k, 1, 1, w_near, w_far, dtype,
                                 FMM_FAR_NORM_PER_MAP, nullptr, p, stream);
   fmm::FwArgs f;
@@ -947,6 +1006,7 @@ int run_fastweight(const void* q, const void* k, const void* v, const float* bet
   f.d = d;
   f.dtype = dtype;
   f.stream = stream;
+  f.pass_bytes = pass;
   f.ws = nullptr;
   EventTimer& t = timer();
   {
@@ -960,13 +1020,12 @@ int run_fastweight(const void* q, const void* k, const void* v, const float* bet
   }
   std::lock_guard<std::mutex> wl(ws_mutex());
   void* ws = nullptr;
-  st = acquire_ws_locked(stream, total, &ws);
+  st = acquire_ws_locked(stream, total, &ws, !*last);
   if (st != FMM_OK) return st;
   a.ws = (float*)ws;
   float* minus_inf =
       reinterpret_cast<float*>(reinterpret_cast<uintptr_t>(ws) + p.ws_bytes);
-  f.ws = reinterpret_cast<float*>(reinterpret_cast<uintptr_t>(ws) + p.ws_bytes +
-                                  align256((size_t)H * 4));
+  f.ws = (float*)ws;
   std::lock_guard<std::mutex> g(t.mu);
   fmm::Launcher L;
   L.timer = &t;
@@ -987,7 +1046,7 @@ int run_backward_fastweight(const void* q, const void* k, const void* v, const f
                             const void* dout, void* dq, void* dk, void* dv, float* dbeta,
                             float* dw_near, float* dw_far, int B, int H, int N, int d,
                             int band_k, int n_linear, const float* w_near, const float* w_far,
-                            int dtype, void* stream) {
+                            int dtype, void* stream, bool lean) {
   int st = validate(q, k, v, dq, B, H, N, d, band_k, 1, 1, w_near, w_far, dtype,
                     FMM_FAR_NORM_PER_MAP);
   if (st != FMM_OK) return st;
@@ -1012,15 +1071,15 @@ int run_backward_fastweight(const void* q, const void* k, const void* v, const f
     if (overlaps2(dbeta, nb, o, bytes)) return FMM_ERR_INVALID_ARG;
   if (overlaps2(dbeta, nb, beta, nb) || overlaps(dw_near, dw_far, (size_t)H * 4))
     return FMM_ERR_INVALID_ARG;
-  const BwdPlan bp = bwd_plan(B, H, N, d, 1, 1, dtype);
+  const BwdPlan bp = bwd_plan(B, H, N, d, 1, 1, dtype, lean);
   if (bp.total == 0) return FMM_ERR_UNSUPPORTED;
-  // after the backward's workspace: H floats of -inf, then the fast-weight
-  // kernels' chunks
+  // the backward's workspace and H floats of -inf, then, once its kernels have
+  // run, the fast-weight kernels' chunks in the same place
   typedef unsigned __int128 u128;
-  const u128 fwb = fmm::fw_backward_bytes((long long)B * H, N, d);
-  const u128 tot = (u128)bp.total + align256((size_t)H * 4) + fwb;
+  const u128 tot = std::max((u128)bp.total + align256((size_t)H * 4),
+                            fmm::fw_backward_bytes((long long)B * H, N, d));
   if (tot > (u128)(SIZE_MAX / 4)) return FMM_ERR_UNSUPPORTED;
-  const size_t off_m = bp.total, off_f = off_m + align256((size_t)H * 4);
+  const size_t off_m = bp.total;
   fmm::LaunchArgs fa = make_args(q, k, v, dq, B, H, N, d, band_k, 1, 1, w_near, w_far, dtype,
                                  FMM_FAR_NORM_PER_MAP, nullptr, bp.p, stream);
   fmm::BwdArgs ba;
@@ -1079,12 +1138,12 @@ int run_backward_fastweight(const void* q, const void* k, const void* v, const f
   }
   std::lock_guard<std::mutex> wl(ws_mutex());
   void* ws = nullptr;
-  st = acquire_ws_locked(stream, (size_t)tot, &ws);
+  st = acquire_ws_locked(stream, (size_t)tot, &ws, !lean);
   if (st != FMM_OK) return st;
   const uintptr_t w = reinterpret_cast<uintptr_t>(ws);
   fa.ws = (float*)ws;
   fill_bwd_args(ba, bp, ws, B, H);
-  fb.ws = reinterpret_cast<float*>(w + off_f);
+  fb.ws = (float*)ws;
   float* minus_inf = reinterpret_cast<float*>(w + off_m);
   std::lock_guard<std::mutex> g(t.mu);
   fmm::Launcher L;
@@ -1152,8 +1211,8 @@ int fmm_attn_backward(const void* q, const void* k, const void* v, const void* d
                       void* dk, void* dv, float* dw_near, float* dw_far, int B, int H, int N,
                       int d, int band_k, int rank, int causal, const float* w_near,
                       const float* w_far, int dtype, void* stream) {
-  return run_backward(q, k, v, dout, dq, dk, dv, dw_near, dw_far, B, H, N, d, band_k, rank,
-                      causal, w_near, w_far, dtype, FMM_FAR_NORM_PER_MAP, stream);
+  return fmm_attn_backward_ex(q, k, v, dout, dq, dk, dv, dw_near, dw_far, B, H, N, d, band_k,
+                              rank, causal, w_near, w_far, dtype, FMM_FAR_NORM_PER_MAP, stream);
 }
 
 int fmm_attn_backward_ex(const void* q, const void* k, const void* v, const void* dout,
@@ -1161,16 +1220,20 @@ int fmm_attn_backward_ex(const void* q, const void* k, const void* v, const void
                          int H, int N, int d, int band_k, int rank, int causal,
                          const float* w_near, const float* w_far, int dtype, int far_norm,
                          void* stream) {
-  return run_backward(q, k, v, dout, dq, dk, dv, dw_near, dw_far, B, H, N, d, band_k, rank,
-                      causal, w_near, w_far, dtype, far_norm, stream);
+  return preferred_or_lean([&](bool lean) {
+    return run_backward(q, k, v, dout, dq, dk, dv, dw_near, dw_far, B, H, N, d, band_k, rank,
+                        causal, w_near, w_far, dtype, far_norm, stream, lean);
+  });
 }
 
 int fmm_attn_layer_backward(const void* x, const void* w_qkv, const void* w_out, const void* dy,
                             void* dx, void* dw_qkv, void* dw_out, float* dw_near, float* dw_far,
                             int B, int N, int E, int H, int band_k, int rank, int causal,
                             const float* w_near, const float* w_far, int dtype, void* stream) {
-  return run_layer_backward(x, w_qkv, w_out, dy, dx, dw_qkv, dw_out, dw_near, dw_far, B, N, E, H,
-                            band_k, rank, causal, w_near, w_far, dtype, stream);
+  return preferred_or_lean([&](bool lean) {
+    return run_layer_backward(x, w_qkv, w_out, dy, dx, dw_qkv, dw_out, dw_near, dw_far, B, N, E,
+                              H, band_k, rank, causal, w_near, w_far, dtype, stream, lean);
+  });
 }
 
 int fmm_attn_backward_fastweight(const void* q, const void* k, const void* v, const float* beta,
@@ -1178,23 +1241,31 @@ int fmm_attn_backward_fastweight(const void* q, const void* k, const void* v, co
                                  float* dw_near, float* dw_far, int B, int H, int N, int d,
                                  int band_k, int n_linear, const float* w_near,
                                  const float* w_far, int dtype, void* stream) {
-  return run_backward_fastweight(q, k, v, beta, dout, dq, dk, dv, dbeta, dw_near, dw_far, B, H,
-                                 N, d, band_k, n_linear, w_near, w_far, dtype, stream);
+  return preferred_or_lean([&](bool lean) {
+    return run_backward_fastweight(q, k, v, beta, dout, dq, dk, dv, dbeta, dw_near, dw_far, B, H,
+                                   N, d, band_k, n_linear, w_near, w_far, dtype, stream, lean);
+  });
 }
 
 int fmm_attn_layer_forward(const void* x, const void* w_qkv, const void* w_out, void* y, int B,
                            int N, int E, int H, int band_k, int rank, int causal,
                            const float* w_near, const float* w_far, int dtype, void* stream) {
-  return run_layer(x, w_qkv, w_out, y, B, N, E, H, band_k, rank, causal, w_near, w_far, dtype,
-                   stream);
+  return preferred_or_lean([&](bool lean) {
+    return run_layer(x, w_qkv, w_out, y, B, N, E, H, band_k, rank, causal, w_near, w_far, dtype,
+                     stream, lean);
+  });
 }
 
 int fmm_attn_forward_fastweight(const void* q, const void* k, const void* v, const float* beta,
                                 void* out, int B, int H, int N, int d, int band_k, int n_linear,
                                 const float* w_near, const float* w_far, int dtype,
                                 void* stream) {
-  return run_fastweight(q, k, v, beta, out, B, H, N, d, band_k, n_linear, w_near, w_far, dtype,
-                        stream);
+  bool last = false;
+  for (int level = 0;; ++level) {
+    const int st = run_fastweight(q, k, v, beta, out, B, H, N, d, band_k, n_linear, w_near, w_far,
+                                  dtype, stream, level, &last);
+    if (last || (st != FMM_ERR_OOM && st != FMM_ERR_UNSUPPORTED)) return st;
+  }
 }
 
 size_t fmm_attn_workspace_bytes(int B, int H, int N, int d, int rank, int causal) {

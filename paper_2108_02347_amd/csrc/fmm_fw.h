@@ -21,26 +21,26 @@ inline size_t fw_chunk_floats(int d, bool bwd) {
 }
 inline long long fw_chunks(int N) { return ((long long)N + kFwChunk - 1) / kFwChunk; }
 
-// The forward runs in passes of at most kFwPassBytes of chunks (whole slices,
-// or, where one slice alone has more, ranges of its chunks with W and z
-// carried from one range to the next), so that its workspace stays small
-// beside q, k, v and out whatever the shape.
+// The forward runs in passes of at most `bytes` of chunks (whole slices, or,
+// where one slice alone has more, ranges of its chunks with W and z carried from
+// one range to the next): up to kFwPassBytes, or what is to be had.  A position
+// takes 5 d + d (d + 1) / 16 + 2 floats (378 at d = 32, 1674 at d = 128).
 constexpr size_t kFwPassBytes = (size_t)1 << 30;
 struct FwPlan {
   long long slices;  // slices per pass
   long long chunks;  // chunks of a slice per pass
 };
-inline FwPlan fw_plan(long long bh, int N, int d) {
+inline FwPlan fw_plan(long long bh, int N, int d, size_t bytes) {
   const long long most = std::max<long long>(
-      1, (long long)(kFwPassBytes / (fw_chunk_floats(d, false) * sizeof(float))));
+      1, (long long)(bytes / (fw_chunk_floats(d, false) * sizeof(float))));
   const long long nc = fw_chunks(N);
   FwPlan p;
   p.chunks = std::min(nc, most);
   p.slices = nc > most ? 1 : std::min(bh, most / nc);
   return p;
 }
-inline size_t fw_forward_bytes(long long bh, int N, int d) {
-  const FwPlan p = fw_plan(bh, N, d);
+inline size_t fw_forward_bytes(long long bh, int N, int d, size_t bytes) {
+  const FwPlan p = fw_plan(bh, N, d, bytes);
   // (the carried state of one slice at the end)
   return ((size_t)(p.slices * p.chunks) * fw_chunk_floats(d, false) + (size_t)d * d + d) *
          sizeof(float);

@@ -221,16 +221,17 @@ hipError_t launch_layer_proj(Launcher& L, LayerProj mode, int dtype, const void*
                              void* o2, int B, int N, int H, int d, hipStream_t s);
 hipError_t launch_layer_wgrad(Launcher& L, int dtype, bool qkv, const void* A, const void* b0,
                               const void* b1, const void* b2, void* C, float* scratch, int B,
-                              int N, int H, int d, hipStream_t s);
+                              int N, int H, int d, hipStream_t s, bool lean);
 // ta (tb): A (B) stored transposed ([K, M] and [Nc, K] row-major).
 hipError_t layer_gemm(void* handle, void* stream, int dtype, const void* A, const void* Bm,
                       void* C, int M, int K, int Nc, bool ta = false, bool tb = false);
 void* layer_blas_handle_create();
 // The layer's weight gradients C [E, Nc] = A^T B (A [M, E], B [M, Nc] of the
 // storage type, C too): per chunk of kWgradChunk tokens into `scratch`
-// (layer_wgrad_scratch_bytes), then summed in chunk order.
+// (layer_wgrad_scratch_bytes; lean: of this library's kernel too, which else
+// takes shorter ones), then summed in chunk order.
 constexpr int kWgradChunk = 1024;
-size_t layer_wgrad_scratch_bytes(int M, int E, int Nc);
+size_t layer_wgrad_scratch_bytes(int M, int E, int Nc, bool lean);
 hipError_t layer_wgrad(void* handle, Launcher& L, void* stream, int dtype, const void* A,
                        const void* Bm, void* C, int M, int E, int Nc, float* scratch);
 // The layer's backward copies: [B N, E] rows -> [B, H, N, d] (split1), and
@@ -250,7 +251,8 @@ struct FwArgs {
   const float* w_far;
   int B, H, N, d, dtype;
   void* stream;
-  float* ws;  // fw_forward_bytes(B * H, N, d), 16-byte aligned
+  size_t pass_bytes;  // chunks of a pass (fw_plan)
+  float* ws;          // fw_forward_bytes(B * H, N, d, pass_bytes), 16-byte aligned
 };
 hipError_t launch_fast_weight(Launcher& L, const FwArgs& a);
 // Its backward (fmm_fastweight.hip): adds the fast-weight part's dq, dk, dv to

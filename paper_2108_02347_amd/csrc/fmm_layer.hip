@@ -447,22 +447,23 @@ hipError_t sum_chunks(Launcher& L, int dtype, const float* part, void* c, int n,
   return L.err;
 }
 
-// Tokens per chunk of k_wgrad: 256, more where that would be over 256 chunks.
-int own_wgrad_chunk(int M) {
+// Tokens per chunk of k_wgrad: 256, more where that would be over 256 chunks
+// (lean: at least those of the rocBLAS form).
+int own_wgrad_chunk(int M, bool lean) {
   const long long c = ((long long)M + 255) / 256;
-  return (int)std::max<long long>(256, (c + 63) / 64 * 64);
+  return (int)std::max<long long>(lean ? kWgradChunk : 256, (c + 63) / 64 * 64);
 }
 }  // namespace
 
-size_t layer_wgrad_scratch_bytes(int M, int E, int Nc) {
-  const int c = layer_proj_applies(E) ? own_wgrad_chunk(M) : kWgradChunk;
+size_t layer_wgrad_scratch_bytes(int M, int E, int Nc, bool lean) {
+  const int c = layer_proj_applies(E) ? own_wgrad_chunk(M, lean) : kWgradChunk;
   return (size_t)((M + (long long)c - 1) / c) * E * Nc * sizeof(float);
 }
 
 hipError_t launch_layer_wgrad(Launcher& L, int dtype, bool qkv, const void* A, const void* b0,
                               const void* b1, const void* b2, void* C, float* scratch, int B,
-                              int N, int H, int d, hipStream_t s) {
-  const int E = H * d, M = (int)((long long)B * N), chunk = own_wgrad_chunk(M);
+                              int N, int H, int d, hipStream_t s, bool lean) {
+  const int E = H * d, M = (int)((long long)B * N), chunk = own_wgrad_chunk(M, lean);
   const int nchunk = (int)((M + (long long)chunk - 1) / chunk), parts = qkv ? 3 : 1;
   (void)by_width(L, dtype, E, [&](auto t, auto e) {
     using T = decltype(t);

@@ -45,3 +45,122 @@ def test_layer_takes_only_the_arrays_it_uses(monkeypatch, dtype):
     monkeypatch.setenv("FMM_ATTN_WS_LIMIT", str(13 * array))
     binding.layer_backward(x, w_qkv, w_out, dy, H, w, w, kw, 1, 0)
     torch.cuda.synchronize()
+
+
+def _records(B, H, N, d, rank, rows):
+    """Bytes of the state records with segments of `rows` rows, and per slice."""
+    return _align(B * H * (-(-N // rows) + 1) * rank * d * (d + 1) * 4)
+
+
+def _quarter_rows(B, H, N, d, rank, dtype):
+    """Rows of a segment whose record is a quarter of its K + V bytes, about 512
+    workgroups: the split that the calls need no more workspace than."""
+    up = lambda x: max(64, -(-x // 64) * 64)
+    return max(up(-(-N // -(-512 // (B * H)))), up(8 * rank * (d + 1) // (2 if dtype == "bf16"
+                                                                          else 4)))
+
+
+def _operands(B, H, N, d, dtype, n=4):
+    w = torch.zeros(H, device="cuda")
+    return [_randn(10 + i, dtype, B, H, N, d, std=d ** -0.25) for i in range(n)], w
+
+
+def _close(got, want, dtype):
+    for a, b in zip(got, want):
+        a, b = a.double(), b.double()
+        assert (a - b).norm() <= (1e-2 if dtype == "bf16" else 1e-5) * b.norm()
+
+
+FORWARD = [(1, 2, 5000, 64, 2, 1, "bf16"), (2, 4, 9000, 128, 2, 1, "bf16"),
+           (1, 2, 5000, 32, 2, 1, "f32"), (1, 1, 3000, 128, 1, 0, "f32")]
+
+
+@pytest.mark.parametrize("B,H,N,d,rank,causal,dtype", FORWARD)
+def test_forward_with_quarter_size_records(monkeypatch, B, H, N, d, rank, causal, dtype):
+    # a caller's buffer, the limit, or a capture that finds no more than the
+    # longer segments' workspace: the call takes those; with more, the preferred
+    # ones
+    (q, k, v), w = _operands(B, H, N, d, dtype, 3)
+    need = _records(B, H, N, d, rank, _quarter_rows(B, H, N, d, rank, dtype))
+    more = _preferred(B, H, N, d, 20, rank, causal, dtype)
+    log(f"forward B={B} H={H} N={N} d={d} r={rank} {dtype}: {need} of {more} bytes")
+    assert need < more
+    args = (q, k, v, w, w, 20, rank, causal)
+    want = binding.forward(*args)
+    ws = torch.empty(more, dtype=torch.uint8, device="cuda")
+    _close([binding.forward_ws(*args, ws[:need])], [want], dtype)
+    assert torch.equal(binding.forward_ws(*args, ws), want)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    monkeypatch.setenv("FMM_ATTN_WS_LIMIT", str(need))
+    with torch.cuda.stream(s):
+        lean = binding.forward(*args)
+    monkeypatch.delenv("FMM_ATTN_WS_LIMIT")
+    torch.cuda.synchronize()
+    _close([lean], [want], dtype)
+    out = torch.empty_like(q)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        binding.forward(*args, out=out)
+    for _ in range(3):
+        out.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, lean)
+
+
+@pytest.mark.parametrize("B,H,N,d,rank,causal,dtype",
+                         FORWARD[:3] + [(8, 2, 4001, 32, 3, 0, "bf16")])
+def test_backward_with_quarter_size_records(monkeypatch, B, H, N, d, rank, causal, dtype):
+    (q, k, v, g), w = _operands(B, H, N, d, dtype)
+    rows = _quarter_rows(B, H, N, d, rank, dtype)
+    limit = (2 * _records(B, H, N, d, rank, rows) + _align(B * H * N * 12)
+             + _align(B * H * N * rank * 8) + _align(B * H * -(-N // rows) * 8))
+    log(f"backward B={B} H={H} N={N} d={d} r={rank} {dtype}: {limit} bytes")
+    args = (q, k, v, g, w, w, 20, rank, causal)
+    joint = dict(joint=rank == 3)
+    want = binding.backward(*args, **joint)
+    monkeypatch.setenv("FMM_ATTN_WS_LIMIT", str(limit))
+    _close(binding.backward(*args, **joint)[:3], want[:3], dtype)
+
+
+@pytest.mark.parametrize("B,H,N,d,dtype", [(16, 8, 256, 16, "f32"), (2, 4, 700, 32, "bf16"),
+                                           (2, 2, 500, 64, "f32"), (1, 3, 200, 128, "bf16")])
+def test_fast_weight_with_the_former_scratch(monkeypatch, B, H, N, d, dtype):
+    # one step per position needed the operator's records and, forward, p(k) and
+    # p(q) of every row for the narrow widths; backward, every W_i and z_i
+    (q, k, v, g), w = _operands(B, H, N, d, dtype)
+    beta = torch.rand(B, H, N, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    rows = _quarter_rows(B, H, N, d, 1, dtype)
+    slices, rec = B * H, _records(B, H, N, d, 1, rows)
+    limit = rec + _align(H * 4) + (8 * slices * N * d if d <= 32 else 0)
+    want = binding.forward_fastweight(q, k, v, beta, w, w, 20, 1)
+    want_b = binding.backward_fastweight(q, k, v, beta, g, w, w, 20, 1)
+    monkeypatch.setenv("FMM_ATTN_WS_LIMIT", str(limit))
+    log(f"fast weight B={B} H={H} N={N} d={d} {dtype}: {limit} bytes")
+    _close([binding.forward_fastweight(q, k, v, beta, w, w, 20, 1)], [want], dtype)
+    limit = (2 * rec + _align(slices * N * 12) + _align(slices * N * 8)
+             + _align(slices * -(-N // rows) * 8) + 4 * slices * N * d * (d + 1)
+             + _align(slices * 4) + _align(H * 4)
+             + (8 * slices * N * (d + 1) if d <= 32 else 0))
+    monkeypatch.setenv("FMM_ATTN_WS_LIMIT", str(limit))
+    _close(binding.backward_fastweight(q, k, v, beta, g, w, w, 20, 1)[:4], want_b[:4], dtype)
+
+
+@pytest.mark.parametrize("H,d", [(8, 16), (4, 64)])
+def test_layer_with_the_former_scratch(monkeypatch, H, d):
+    # E = 128 through this library's products (more chunks of weight gradients),
+    # 256 through rocBLAS; both with quarter-size records
+    B, N, kw, rank, dtype = 2, 1500, 5, 2, "bf16"
+    E = H * d
+    x, dy = (_randn(i, dtype, B, N, E) for i in (1, 2))
+    w_qkv, w_out = (_randn(i, dtype, E, c, std=E ** -0.5) for i, c in ((3, 3 * E), (4, E)))
+    w = torch.zeros(H, device="cuda")
+    want = binding.layer_backward(x, w_qkv, w_out, dy, H, w, w, kw, rank, 1)
+    rows = _quarter_rows(B, H, N, d, rank, dtype)
+    rec, array = _records(B, H, N, d, rank, rows), _align(B * N * E * 2)
+    limit = (13 * array + 3 * rec + _align(B * H * N * 12) + _align(B * H * N * rank * 8)
+             + _align(B * H * -(-N // rows) * 8) + -(-B * N // 1024) * E * 3 * E * 4)
+    log(f"layer backward E={E}: {limit} bytes")
+    monkeypatch.setenv("FMM_ATTN_WS_LIMIT", str(limit))
+    _close(binding.layer_backward(x, w_qkv, w_out, dy, H, w, w, kw, rank, 1)[:3], want[:3], dtype)

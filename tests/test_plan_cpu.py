@@ -1,15 +1,23 @@
-"""The forward's split into state segments, seen through its workspace: one
-record of rank * d * (d + 1) floats per segment and one per slice, for the
-storage type that needs more.  No GPU is used."""
+"""The forward's split into state segments, seen through the workspace of its
+plan: one record of rank * d * (d + 1) floats per segment and one per slice.  No
+GPU is used."""
+
+import ctypes
 
 import pytest
 
 from paper_2108_02347_amd import binding
 
 
+def plan_bytes(B, H, N, d, rank, causal, bf16):
+    f = binding.lib()._ZN3fmm23forward_workspace_bytesEiiiiiiii  # fmm::forward_workspace_bytes
+    f.restype = ctypes.c_size_t
+    return f(B, H, N, d, 5, rank, causal, int(bf16))
+
+
 def segments(B, H, N, d, rank, causal=1):
     rec = rank * d * (d + 1) * 4
-    return binding.workspace_bytes(B, H, N, d, rank, causal) // rec - B * H
+    return max(plan_bytes(B, H, N, d, rank, causal, t) for t in (0, 1)) // rec - B * H
 
 
 @pytest.mark.parametrize("B,H,N,d,rank,most", [
@@ -28,4 +36,4 @@ def test_segments_fill_the_chip():
     # 16 workgroups with a quarter-size record rule; at least four times as many
     assert segments(1, 2, 5000, 64, 2) >= 64
     # and within the no-allocation call's array wherever the quarter rule was
-    assert binding.workspace_bytes(2, 4, 16381, 128, 2, 1) <= binding.noalloc_max_bytes()
+    assert plan_bytes(2, 4, 16381, 128, 2, 1, 1) <= binding.noalloc_max_bytes()
