@@ -120,6 +120,31 @@ __device__ __forceinline__ f32x4 contract(const Q* a, const Q* b, f32x4 c) {
   return c;
 }
 
+// The same from zero in fp32, as S accumulators (2 or 4) added in pairs: the
+// partial sums are shorter by that factor, and so is what their rounding adds up
+// to, for S - 1 more vector additions.
+template <int NB, int S = 4>
+__device__ __forceinline__ f32x4 contract_split(const float4* a, const float4* b) {
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4 c[S];
+#pragma unroll
+  for (int i = 0; i < S; ++i) c[i] = zero;
+#pragma unroll
+  for (int t = 0; t < NB; ++t) {
+    c[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t].x, b[t].x, c[0], 0, 0, 0);
+    c[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t].y, b[t].y, c[1], 0, 0, 0);
+    c[2 % S] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t].z, b[t].z, c[2 % S], 0, 0, 0);
+    c[3 % S] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t].w, b[t].w, c[3 % S], 0, 0, 0);
+  }
+  if constexpr (S == 2) return c[0] + c[1];
+  else return (c[0] + c[1]) + (c[2] + c[3]);
+}
+// (bf16: the operands' rounding is far above that of the sums)
+template <int NB, int S = 4>
+__device__ __forceinline__ f32x4 contract_split(const uint2* a, const uint2* b) {
+  return contract<NB>(a, b, f32x4{0.f, 0.f, 0.f, 0.f});
+}
+
 // ---------------------------------------------------------------- maps
 // phi_1(x) = elu(x) + 1 and phi_2(x) = elu(-x) + 1 share e = exp(-|x|).
 // Since exp(y) >= 1 + y for every y, phi_1(x) = max(1 + x, e) (for x > 0, e <

@@ -102,7 +102,8 @@ void launch_merge(Launcher& L, const void* o, void* m, int B, int N, int H, int 
 // product is formed transposed, D[c][t], so that a lane ends with four
 // consecutive columns of one token, stored together.  4096 tokens, E = 128,
 // fp32: 13.9 + 6.2 us, where the two rocBLAS products and the head split and
-// merge took 9.4 + 9.4 + 6.4 + 4.3.
+// merge took 9.4 + 9.4 + 6.4 + 4.3.  fp32 sums in two parts: with one chain of
+// up to 384 products dx was up to 1.08 times as far from float64 as rocBLAS's.
 enum { kProjQkv, kProjOut, kProjDm, kProjDx };
 
 // Token t as (batch, position), and the offset of its column c of E in a
@@ -179,7 +180,7 @@ __global__ __launch_bounds__(256) void k_proj(const T* __restrict__ in0,
     for (int kb = 0; kb < KB; ++kb)
       a[kb] = C::WT ? ld_quad(wl, 16 * cb + r, 16 * kb + 4 * g, C::ST)
                     : ld_tquad(wl, 16 * kb, 16 * cb, C::ST);
-    const f32x4 acc = contract<KB>(a, x, f32x4{0.f, 0.f, 0.f, 0.f});
+    const f32x4 acc = contract_split<KB, 2>(a, x);
     if (!ok) continue;
     const float f[4] = {acc[0], acc[1], acc[2], acc[3]};
     const int c = cc0 + 16 * cb + 4 * g;
@@ -299,7 +300,9 @@ __global__ __launch_bounds__(256) void k_wgrad(const T* __restrict__ A, const T*
           Q aq[4];
 #pragma unroll
           for (int m = 0; m < 4; ++m) aq[m] = ld_tquad(sa, 16 * m, 16 * e, ST);
-          acc[e][x] = contract<4>(aq, bq, acc[e][x]);
+          if constexpr (sizeof(T) == 4)
+            acc[e][x] += contract<4>(aq, bq, f32x4{0.f, 0.f, 0.f, 0.f});
+          else acc[e][x] = contract<4>(aq, bq, acc[e][x]);
         }
       }
     }
