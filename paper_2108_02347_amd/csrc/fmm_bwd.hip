@@ -100,8 +100,6 @@ struct BwdCfg {
   static constexpr int UL = D <= 64 ? R : 1;
 };
 
-__device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7"); }
-
 constexpr int SWB = 8;          // waves of k_seg_grad
 constexpr int SNTB = SWB * 64;
 
@@ -480,6 +478,7 @@ __device__ __forceinline__ float near_hold(f32x4* dq, const typename QuadOf<T>::
         sc[gi][b] = contract<NB>(ka, qq, zero);
         dp[gi][b] = contract<NB>(va, gq, zero);
       }
+      mfma_drain();  // (read on both sides of the branch)
       const bool interior = j0 >= 0 && j0 + 31 < N && j0 >= i0 + 15 - band_k &&
                             (CAUSAL ? j0 + 31 <= i0 : j0 + 31 <= i0 + band_k);
       if (!interior) {
@@ -497,7 +496,6 @@ __device__ __forceinline__ float near_hold(f32x4* dq, const typename QuadOf<T>::
         for (int i = 0; i < 4; ++i) m = fmaxf(m, sc[gi][b][i]);
     }
   }
-  mfma_drain();
   m = col_max(m);
   ms = (m == -INFINITY ? 0.f : m) * scale2;
   float l = 0.f, gn = 0.f;

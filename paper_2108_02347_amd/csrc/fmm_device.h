@@ -145,6 +145,12 @@ __device__ __forceinline__ f32x4 contract_split(const uint2* a, const uint2* b) 
   return contract<NB>(a, b, f32x4{0.f, 0.f, 0.f, 0.f});
 }
 
+// Wait states between matrix-core results and vector instructions that read
+// them across a branch (the end of a loop, a choice made by the whole wave): the
+// distance is given here instead of relying on the compiler's count across
+// branches, which comes out short on paths that skip a block.
+__device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7"); }
+
 // ---------------------------------------------------------------- maps
 // phi_1(x) = elu(x) + 1 and phi_2(x) = elu(-x) + 1 share e = exp(-|x|).
 // Since exp(y) >= 1 + y for every y, phi_1(x) = max(1 + x, e) (for x > 0, e <

@@ -307,7 +307,7 @@ __global__ __launch_bounds__(256) void k_wgrad(const T* __restrict__ A, const T*
       }
     }
   }
-  asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7");  // (results read after the loop's branches)
+  mfma_drain();  // (results read after the loop's branches)
   const int row = E * (int)gridDim.y;
   float* o = part + (size_t)blockIdx.x * E * row + blockIdx.y * E;
 #pragma unroll

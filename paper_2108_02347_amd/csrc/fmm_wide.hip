@@ -52,12 +52,6 @@ struct WideCfg {
   static constexpr int LDS = REC_OFF + REC_BYTES;
 };
 
-// Wait states after a loop whose last matrix-core results are read by vector
-// instructions after the loop exits: the required distance is provided here
-// explicitly instead of relying on the hazard tracking across the loop's
-// branches.
-__device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7"); }
-
 // Rows [ks, ks + nk) of K and V (rows at or beyond kend read as zero) into
 // row-major LDS buffers of stride ST.
 template <typename T, int D>

@@ -35,8 +35,6 @@ constexpr int lds_bytes(int R, bool causal, int U) {
 }
 constexpr int kMaxLds = 160 * 1024;
 
-__device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7"); }
-
 // phi_{l+1} of a chunk of 8 bf16 values (zero where !ok)
 __device__ __forceinline__ uint4 phi_chunk(const uint4& x, int l, bool ok) {
   const uint16_t* e = reinterpret_cast<const uint16_t*>(&x);

@@ -1,0 +1,140 @@
+"""The generated code keeps the wait states between a matrix-core instruction and
+the vector instructions that read its result.  Within straight code the compiler
+puts 8 (16x16x32 bf16) or 10 (16x16x4 fp32) between them; across branches its
+count can come out shorter (a build whose state update sat behind a branch read a
+result two instructions after it, and the sums were wrong).  The test walks every
+path from every matrix instruction of the library built here: a short count is
+accepted only behind a taken branch, which restarts the instruction fetch, and
+then not below four.  No GPU is used."""
+
+import collections
+import glob
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2108_02347_amd import binding
+
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+NEED = {"v_mfma_f32_16x16x32_bf16": 8, "v_mfma_f32_16x16x4_f32": 10}
+PASSES = {"v_mfma_f32_16x16x32_bf16": 4, "v_mfma_f32_16x16x4_f32": 8}
+STORES = ("buffer_store", "global_store", "ds_write", "global_atomic")
+
+
+def _functions(path):
+    text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--mcpu=gfx950", path],
+                          capture_output=True, text=True, check=True).stdout
+    name, ins = None, []
+    for line in text.splitlines():
+        m = re.match(r"^[0-9a-f]+ <(.*)>:$", line)
+        if m:
+            if ins:
+                yield name, ins
+            name, ins = m.group(1), []
+            continue
+        m = re.match(r"^\s+(\S+)\s*(.*?)\s*// ([0-9A-F]+):(.*)$", line)
+        if m:
+            ins.append((int(m.group(3), 16), m.group(1), m.group(2), m.group(4)))
+    if ins:
+        yield name, ins
+
+
+def _registers(operand):
+    m = re.match(r"^[-|]*([va])\[(\d+):(\d+)\]", operand) or \
+        re.match(r"^[-|]*([va])(\d+)(?=\D|$)", operand)
+    if not m:
+        return frozenset()
+    hi = m.group(3) if m.lastindex == 3 else m.group(2)
+    return frozenset((m.group(1), i) for i in range(int(m.group(2)), int(hi) + 1))
+
+
+def _reads_writes(mnemonic, operands):
+    ops = [_registers(o) for o in re.split(r",\s*(?![^\[]*\])", operands)] if operands else []
+    none = frozenset()
+    if mnemonic.startswith("s_") or not ops:
+        return none, none
+    rest = none.union(*ops[1:])
+    if mnemonic.startswith(STORES):
+        return rest | ops[0], none
+    if mnemonic.startswith(("v_fmac", "v_mac")):
+        rest |= ops[0]
+    if "swap" in mnemonic:
+        return rest | ops[0], ops[0] | ops[1]
+    return rest, ops[0]
+
+
+def _short_reads(ins):
+    """(matrix instruction, states, behind a taken branch) of reads nearer than
+    straight code has them."""
+    at = {x[0]: i for i, x in enumerate(ins)}
+    rw = [_reads_writes(m, o) for _, m, o, _ in ins]
+
+    def next_of(i):
+        _, m, _, tail = ins[i]
+        follow = [(i + 1, False)] if i + 1 < len(ins) else []
+        if m == "s_endpgm":
+            return []
+        if not m.startswith(("s_branch", "s_cbranch")):
+            return follow
+        t = re.search(r"<[^>]*?(?:\+0x([0-9a-f]+))?>", tail)
+        target = ins[0][0] + int(t.group(1) or "0", 16) if t else None
+        jump = [(at[target], True)] if target in at else []
+        return jump if m == "s_branch" else jump + follow
+
+    found = []
+    for i, (_, m, o, _) in enumerate(ins):
+        if m not in NEED:
+            continue
+        live = _registers(re.split(r",\s*(?![^\[]*\])", o)[0])
+        stack, seen = [(j, 0, b, live) for j, b in next_of(i)], {}
+        while stack:
+            j, n, taken, live = stack.pop()
+            if n >= NEED[m] or not live:
+                continue
+            old = seen.get((j, taken))
+            if old and old[0] <= n and old[1] >= live:
+                continue
+            seen[j, taken] = (n, live)
+            mj, oj = ins[j][1], ins[j][2]
+            reads, writes = rw[j]
+            if mj in NEED:  # (the matrix pipe orders its own)
+                live = live - reads
+            elif reads & live:
+                found.append((m, n, taken))
+                live = live - reads
+            live = live - writes
+            step = PASSES.get(mj, 1)
+            if mj == "s_nop":
+                step = int(oj.split()[0], 0) + 1
+            stack += [(k, n + step, taken or b, live) for k, b in next_of(j)]
+    return found
+
+
+def test_matrix_results_are_not_read_early(tmp_path):
+    if not os.path.exists(OBJDUMP):
+        pytest.skip("llvm-objdump is missing")
+    lib = shutil.copy(binding.LIB_PATH, tmp_path)
+    subprocess.run([OBJDUMP, "--offloading", lib], check=True, capture_output=True, cwd=tmp_path)
+    objects = glob.glob(str(tmp_path / "*gfx950"))
+    assert objects
+    matrix, short = 0, collections.Counter()
+    for path in objects:
+        for name, ins in _functions(path):
+            matrix += sum(x[1] in NEED for x in ins)
+            for m, n, taken in _short_reads(ins):
+                assert taken and n >= 4, f"{name}: {m} read after {n} states, branch taken: {taken}"
+                short[m, n] += 1
+    assert matrix > 10000
+    print(f"{matrix} matrix instructions; behind a taken branch: {sorted(short.items())}")
+
+
+def test_a_planted_early_read_is_found():
+    line = [(0, "v_mfma_f32_16x16x32_bf16", "v[4:7], v[8:11], v[12:15], v[4:7]", ""),
+            (8, "s_cbranch_scc0", "2", " <k+0x10>"), (12, "s_nop", "7", ""),
+            (16, "v_rcp_f32_e32", "v0, v4", "")]
+    assert _short_reads(line) == [("v_mfma_f32_16x16x32_bf16", 1, True)]
+    line[1] = (8, "s_nop", "7", "")
+    assert _short_reads(line) == []
