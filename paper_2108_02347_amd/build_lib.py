@@ -1,7 +1,9 @@
-"""Builds libfmm_attn.so in-tree with hipcc for gfx950, and _fmm_torch.so, the
-torch.autograd functions over it, with the host compiler.
+"""Builds libfmm_attn.so in-tree with hipcc for gfx950, and, where torch is
+installed, _fmm_torch.so, the torch.autograd functions over it, with the host
+compiler.
 
-Usage: python -m paper_2108_02347_amd.build_lib   (or call build())
+Usage: python -m paper_2108_02347_amd.build_lib   (or call build(); without
+torch, which the package needs, run this file by its path)
 """
 
 from __future__ import annotations
@@ -28,7 +30,6 @@ VARIANTS = [
     # registers beside the vector registers
     ("fmm_bwd.hip", "fmm_bwd_f32_d128", ["-DFMM_BWD_F32_D128"], False),
 ]
-HEADERS = ["fmm_device.h", "fmm_launch.h", "fmm_oct.h", "fmm_apply.h", "fmm_fw.h"]
 
 
 def hipcc() -> str:
@@ -53,10 +54,14 @@ def _flags(vgpr_form: bool = True):
 
 
 def _torch_ext_cmds(obj: str):
-    """Compile and link commands of the extension module (host code only)."""
+    """Compile and link commands of the extension module (host code only), or
+    None without torch: the library itself needs hipcc alone."""
     import sysconfig
 
-    import torch
+    try:
+        import torch
+    except ImportError:
+        return None
     tdir = os.path.dirname(torch.__file__)
     cxx = os.environ.get("CXX") or shutil.which("g++") or "g++"
     inc = [os.path.join(tdir, "include"),
@@ -79,6 +84,7 @@ def build(verbose: bool = False) -> str:
     translation units are compiled in parallel, then linked."""
     cc = hipcc()
     tmpdir = tempfile.mkdtemp(prefix="fmm_build_")
+    ext_proc = None
     try:
         objs, procs = [], []
         units = [(src, src, [], True) for src in SOURCES] + VARIANTS
@@ -91,11 +97,12 @@ def build(verbose: bool = False) -> str:
                                                  stderr=subprocess.STDOUT, text=True)))
             objs.append(obj)
         ext_obj = os.path.join(tmpdir, "fmm_torch.o")
-        ext_compile, ext_link = _torch_ext_cmds(ext_obj)
-        if verbose:
-            print(" ".join(ext_compile), flush=True)
-        procs.append(("fmm_torch.cpp", subprocess.Popen(ext_compile, stdout=subprocess.PIPE,
-                                                        stderr=subprocess.STDOUT, text=True)))
+        ext = _torch_ext_cmds(ext_obj)
+        if ext:
+            if verbose:
+                print(" ".join(ext[0]), flush=True)
+            ext_proc = subprocess.Popen(ext[0], stdout=subprocess.PIPE, stderr=subprocess.STDOUT,
+                                        text=True)
         failed = []
         for src, pr in procs:
             out, _ = pr.communicate()
@@ -116,15 +123,25 @@ def build(verbose: bool = False) -> str:
             sys.stderr.write(res.stdout + res.stderr)
             raise RuntimeError(f"hipcc link failed with status {res.returncode}")
         os.replace(LIB + ".tmp", LIB)
+        if not ext:
+            print("torch is not installed: _fmm_torch.so is not built", file=sys.stderr)
+            return LIB
         # the extension links against the library just built
+        out, _ = ext_proc.communicate()
+        if ext_proc.returncode != 0:
+            sys.stderr.write(out)
+            raise RuntimeError("compiling fmm_torch.cpp failed")
         if verbose:
-            print(" ".join(ext_link), flush=True)
-        res = subprocess.run(ext_link, capture_output=True, text=True)
+            print(" ".join(ext[1]), flush=True)
+        res = subprocess.run(ext[1], capture_output=True, text=True)
         if res.returncode != 0:
             sys.stderr.write(res.stdout + res.stderr)
             raise RuntimeError(f"linking _fmm_torch.so failed with status {res.returncode}")
         os.replace(TORCH_EXT + ".tmp", TORCH_EXT)
     finally:
+        if ext_proc is not None and ext_proc.returncode is None:
+            ext_proc.kill()
+            ext_proc.wait()
         shutil.rmtree(tmpdir, ignore_errors=True)
     return LIB
 
