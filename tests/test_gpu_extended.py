@@ -52,8 +52,9 @@ def check(B, H, N, d, kw, rank, causal, dtype, joint, seed, shift=0.0, std=1.0):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("causal", [0, 1])
 def test_width_128(dtype, causal):
-    # several tiles and state segments per slice, bands narrower and wider
-    # than a staging round, a ragged tail
+    # several tiles (causal, one workgroup's; non-causal, one each) and state
+    # segments per slice, bands narrower and wider than a staging round, a ragged
+    # tail
     worst = 0.0
     for B, H, N, kw, rank in ((2, 2, 2000, 64, 2), (1, 3, 777, 5, 1), (1, 1, 1500, 300, 2),
                               (3, 1, 64, 0, 2)):

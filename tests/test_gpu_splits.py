@@ -1,7 +1,8 @@
 """Work splits of the non-causal calls: the row segments walked by the apply,
 row and key passes are chosen apart from the state segments, so shapes whose
 two splits differ (short and long slices, a ragged last segment, a last
-segment of one row) are compared with the float64 oracle."""
+segment of one row) are compared with the float64 oracle.  Their row segments
+are one tile long; longer ones are in test_gpu_long_walks.py."""
 
 import pytest
 

@@ -1,6 +1,8 @@
 """bf16 heads of 128 (k_wide128) against the float64 oracle where its dispatch
 and its ring turn: both forms, one and two maps, both normalisations, bands at
-and past the ring's units, one tile, ragged tails and several segments."""
+and past the ring's units, one tile, ragged tails and several segments.  The
+causal walks turn the ring here; the non-causal ones take one tile per workgroup
+at these lengths, longer ones are in test_gpu_long_walks.py."""
 
 import numpy as np
 import pytest
