@@ -487,7 +487,9 @@ BwdPlan bwd_plan(int B, int H, int N, int d, int rank, int causal, int dtype,
   // 133; 8 of 9000, rank 1, 232 of 320 81, 376 of 192 75.  fp32, rank 2, 8 of
   // 9000: 232 of 320 266 us, 376 of 192 319
   const int es = dtype == FMM_DTYPE_BF16 ? 2 : 4;
-  const int round2 = !causal ? 21 : es == 2 ? 16 : 17;
+  // (causal, three maps at d = 64: one workgroup per CU, 32 slices of 4000 rows
+  // 370 us with 512 workgroups, 336 with 256)
+  const int round2 = !causal ? 21 : rank == 3 && d == 64 ? 20 : es == 2 ? 16 : 17;
   const long long bh = (long long)B * H;
   b.p = make_plan(B, H, N, d, rank,
                   lean ? segment_rows(bh, N, d, rank, es)

@@ -1515,9 +1515,12 @@ hipError_t launch_bwd_dcf(const BwdArgs& a, Launcher& L) {
 template <typename T, int D, int R>
 hipError_t launch_bwd_r(const BwdArgs& a, Launcher& L) {
   // at d <= 64 the state leaves room for two workgroups per CU (two waves per
-  // SIMD) where a staging round then still holds a tile
+  // SIMD) where a staging round then still holds a tile; not for the causal
+  // passes of three maps at d = 64, which spill within 256 registers (194 in the
+  // bf16 key pass; forward and backward, 8 slices of 4001 rows: 273 us, 206 with
+  // one workgroup; d = 32: 161 against 176)
   constexpr bool two = D <= 64 && BwdCfg<T, D, R, true>::FITS;
-  return a.causal ? launch_bwd_dcf<T, D, true, R, two>(a, L)
+  return a.causal ? launch_bwd_dcf<T, D, true, R, two && !(D == 64 && R == 3)>(a, L)
                   : launch_bwd_dcf<T, D, false, R, two>(a, L);
 }
 
