@@ -109,8 +109,8 @@ def trace_summary(stats_csv):
         _, dur = _durations(disp, needle)
         instep[key] = statistics.mean(dur[warm * per:(warm + steps) * per])
         events[key] = statistics.mean(dur[(warm + steps) * per:(warm + 2 * steps) * per])
-    for key, needle in (("combine_noncausal", "k_state_combine<false>"),
-                        ("combine_causal", "k_state_combine<true>")):
+    for key, needle in (("combine_noncausal", "k_state_combine<false, false>"),
+                        ("combine_causal", "k_state_combine<true, false>")):
         _, dur = _durations(disp, needle)
         instep[key] = statistics.mean(dur[warm:warm + steps])
         events[key] = statistics.mean(dur[warm + steps:warm + 2 * steps])
@@ -292,7 +292,9 @@ def read_counters(kernel: str):
 # the sources of the kernels the profiles describe (host-side code excluded,
 # so a change to argument checks or bindings does not void them)
 KERNEL_SOURCES = ("fmm_device.h", "fmm_oct.h", "fmm_apply.h", "fmm_launch.h", "fmm_xchg.h",
-                  "fmm_kernels.hip", "fmm_pair.hip", "fmm_causal.hip")
+                  "fmm_kernels.hip", "fmm_pair.hip", "fmm_causal.hip", "fmm_wide.hip",
+                  "fmm_wide128.hip", "fmm_bwd.hip", "fmm_fw.h", "fmm_fastweight.hip",
+                  "fmm_layer.hip")
 
 
 def kernel_source_hash() -> str:
@@ -762,8 +764,8 @@ def main():
     yl = torch.empty_like(xl)
     tl = timed(lambda: binding.layer_forward(xl, wl, wo, H4, wn4, wf4, w4.band_k, w4.rank, 0,
                                              out=yl), args.steps, args.warmup, torch)
-    # its backward (the forward recomputed, rocBLAS projections, the
-    # operator's backward), with the forward's output as dy
+    # its backward (the forward recomputed, the projections' and the operator's
+    # backward, the weight gradients), with the forward's output as dy
     tlb = timed(lambda: binding.layer_backward(xl, wl, wo, yl, H4, wn4, wf4, w4.band_k, w4.rank,
                                                0), args.steps, args.warmup, torch)
     layer_rec = {"shape": "B=8 N=4096 E=64 H=2 (d=32) bf16 k=20 rank=2 non-causal",
@@ -782,21 +784,25 @@ def main():
     of = torch.empty_like(qf)
     tfw = timed(lambda: binding.forward_fastweight(qf, kf, vf, bf, wnf, wff, wl4.band_k, 1,
                                                    out=of), args.steps, args.warmup, torch)
-    for name in binding.KERNELS:
-        binding.kernel_timing_read(name)
-    binding.kernel_timing(True)
-    timed(lambda: binding.forward_fastweight(qf, kf, vf, bf, wnf, wff, wl4.band_k, 1, out=of),
-          args.steps, 0, torch)
-    binding.kernel_timing(False)
+    # (a pass with events first: with 6 us kernels the cost of the new events
+    # shows, 56 us of them in a call of 38)
+    for _ in range(2):
+        for name in binding.KERNELS:
+            binding.kernel_timing_read(name)
+        binding.kernel_timing(True)
+        timed(lambda: binding.forward_fastweight(qf, kf, vf, bf, wnf, wff, wl4.band_k, 1, out=of),
+              args.steps, 0, torch)
+        binding.kernel_timing(False)
     ms_fw, n_fw = binding.kernel_timing_read("fast_weight")
     # its backward (the operator's backward at rank 1 plus the fast-weight
-    # sweeps), with the forward's output as the upstream gradient
+    # kernels), with the forward's output as the upstream gradient
     tfwb = timed(lambda: binding.backward_fastweight(qf, kf, vf, bf, of, wnf, wff, wl4.band_k,
                                                      1), args.steps, args.warmup, torch)
     fw_rec = {"shape": "B=16 H=8 N=256 d=16 f32 k=20, fast weight + linear far field, causal",
               "ms_per_call": round(tfw * 1e3, 4),
               "tokens_per_s": round(wl4.B * wl4.N / tfw, 1),
-              # the normalisation pass and the sequential scan, per call
+              # its three kernels (before, in and after the scan), with events
+              # attached, per call
               "fast_weight_kernels_us_per_call": round(ms_fw * 1e3 / args.steps, 3)
               if n_fw else None,
               "backward_ms_per_call": round(tfwb * 1e3, 4)}

@@ -37,10 +37,13 @@ struct Plan {
   int fused_g = 0;  // workgroups per slice of the one-launch path (0: not available)
 };
 
-// The one-launch path for short non-causal slices is planned for MI355X's 256
-// compute units at two workgroups each; a device with fewer CUs (checked per
+// Plans are made for MI355X's 256 compute units.
+constexpr long long kCUs = 256;
+
+// The one-launch path for short non-causal slices is planned at two workgroups
+// per compute unit; a device with fewer CUs (checked per
 // call) takes the three-launch path with the same workspace.
-constexpr int kFusedPlanWorkgroups = 512;
+constexpr int kFusedPlanWorkgroups = 2 * kCUs;
 
 // Rows per segment so that B*H*segments is about `target_wg` workgroups.
 long long seg_rows(long long bh, int N, long long target_wg, int tm) {
@@ -61,7 +64,7 @@ long long record_rows(int d, int rank, int esize, int share) {
 // Rows of a state segment: ~512 workgroups, each segment's state record
 // (rank*d*(d+1) floats) at most a quarter of the K+V bytes it summarises.
 long long segment_rows(long long bh, int N, int d, int rank, int esize) {
-  return std::max(seg_rows(bh, N, 512, fmm::tile_rows()), record_rows(d, rank, esize, 4));
+  return std::max(seg_rows(bh, N, 2 * kCUs, fmm::tile_rows()), record_rows(d, rank, esize, 4));
 }
 
 // Shorter ones, records of up to the K+V bytes themselves, where they leave at
@@ -76,10 +79,9 @@ long long fill_rows(long long bh, int N, int d, int rank, int esize, long long w
   if (n < 1) return base;
   const int tm = fmm::tile_rows();
   const long long l = ((N + n - 1) / n + tm - 1) / tm * tm;
-  return std::min(base, std::max({l, seg_rows(bh, N, 512, tm), record_rows(d, rank, esize, 1)}));
+  return std::min(base, std::max({l, seg_rows(bh, N, 2 * kCUs, tm), record_rows(d, rank, esize, 1)}));
 }
 
-constexpr long long kCUs = 256;
 // Segments of a slice beyond which the combine, which walks a slice's records
 // in four ranges and keeps the first 32 of each in registers, costs more than
 // the shorter walks save (one slice of 30000 rows, causal, us: bf16, d = 32,
@@ -107,7 +109,7 @@ long long one_or_two_rows(long long bh, int N, int d, int rank, int esize, long 
 Plan make_plan(int B, int H, int N, int d, int rank, long long L, int apply_tm) {
   const long long bh = (long long)B * H;
   // non-causal apply walk: ~512 workgroups (two per CU), no state per segment
-  const long long La = seg_rows(bh, N, 512, apply_tm);
+  const long long La = seg_rows(bh, N, 2 * kCUs, apply_tm);
   Plan p;
   p.L = (int)L;
   p.nseg = (int)((N + L - 1) / L);

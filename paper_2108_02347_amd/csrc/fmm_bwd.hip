@@ -93,9 +93,11 @@ struct BwdCfg {
   // B are rings of 128 rows (row j at j mod 128), and only the 64 rows that the
   // next tile adds are loaded, while the current tile computes
   static constexpr bool RING = D * (int)sizeof(T) <= 128 && WK >= 128;
-  // row pass: the tile's own rows loaded a tile ahead (157 us; 161 without); the
-  // key pass spills for it (251 us; 218 without); and maps unrolled (at d = 128
-  // the registers do not hold either)
+  // the row pass loads the tile's own q and dout rows a tile ahead (8 slices of
+  // 65536 rows, d = 64, rank 2, k = 64, causal, bf16: 157 us; 161 without); the
+  // key pass loads its k and v rows when the tile starts (a tile ahead it spilled:
+  // 251 us; 218 so).  Both unroll the maps.  Not at d = 128, whose registers hold
+  // neither; the narrower widths, with fewer registers, follow d = 64
   static constexpr bool AHEAD = D <= 64;
   static constexpr int UL = D <= 64 ? R : 1;
 };

@@ -242,8 +242,9 @@ __global__ __launch_bounds__(NT8) void k_wide128(const T* __restrict__ q,
         }
         if (l + 1 < R) {
           __syncthreads();  // every wave has read map l's phi rows
-          // the next map's, from the tile's key rows in the ring (kept in
-          // registers from the prefetch they would spill)
+          // the next map's, from the tile's key rows in the ring (the causal
+          // form of two maps already spills 26 to 31 registers; kept from the
+          // prefetch they would be eight more)
 #pragma unroll
           for (int it = 0; it < Rows::IT; ++it) {
             const int x = threadIdx.x + it * NT8, i = x / Rows::CPR, c = 8 * (x % Rows::CPR);
