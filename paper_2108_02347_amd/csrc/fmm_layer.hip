@@ -369,6 +369,9 @@ hipError_t launch_layer_copy(Launcher& L, bool split, int dtype, const void* src
   return L.err;
 }
 
+// Any number of tokens (whole causal layer calls, rocBLAS with head copies ->
+// these, us: E = 32, 64 tokens fp32 30 -> 20, bf16 20 -> 20; 262144 tokens fp32
+// 318 -> 164, bf16 82 -> 77; E = 128 34 -> 22, 23 -> 21; 1194 -> 808, 403 -> 353).
 bool layer_proj_applies(int E) { return E == 32 || E == 64 || E == 96 || E == 128; }
 
 hipError_t launch_layer_proj(Launcher& L, LayerProj mode, int dtype, const void* i0,
